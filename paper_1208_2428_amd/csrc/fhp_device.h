@@ -66,192 +66,181 @@ FHP_HD uint32_t or3(uint32_t a, uint32_t b, uint32_t c) { return lop3<kA | kB | 
 // Rule sets (the values of fhp_params.rules).
 constexpr int kRulesFHP2 = 0, kRulesFHP1 = 1, kRulesFHP3 = 2;
 
-// Particle counts of the six moving channels of 32 nodes, by parity class:
-// even class (0, 2, 4) count = 2 ce + se, odd class (1, 3, 5) = 2 co + so;
-// total n = n0 + 2 n1 + 4 n2; pp = a head-on pair is present; eq024 =
-// channels 0, 2, 4 all equal.
-struct Counts {
-    uint32_t se, ce, so, co, n0, n1, n2, pp, eq024;
+// Collisions of 32 nodes after streaming (fluid nodes) and bounce-back (solid
+// nodes).  a[0..5] moving channels, a[6] rest, s solid, chi chirality.
+//
+// Every rule is applied as flips, shared by as many channels as possible:
+//   o_j = a_j ^ E_k ^ V_class
+// with one mask E_k per pair of opposite channels (k = j mod 3, the channels k
+// and k+3) and one mask V per parity class (even channels 0, 2, 4, odd
+// channels 1, 3, 5; neighbouring channels lie in different classes, channels
+// 120 degrees apart in the same one).  With y_k = a_k ^ a_{k+3}:
+//   bounce-back of a solid node exchanges the channels of every pair:
+//     E_k = y_k;
+//   R1, a head-on pair alone (rest particle a spectator) turns by +60 deg
+//     (chi = 1) or -60 deg (chi = 0): its own pair and the one it turns to
+//     flip; each pair is all set or all clear, so that is every k but the one
+//     left alone: E_k = ~(chi ? a_{k+1} : a_{k+2});
+//   R2, {0,2,4} <-> {1,3,5}: every y_k is set and all six flip: E_k = y_k;
+//   R3, one particle c plus rest <-> {c-1, c+1} without rest.  One class is
+//     empty.  E_k = y_k, plus the whole empty class flips: E_k moves each
+//     particle to its opposite channel, and flipping the empty class turns
+//     what has arrived there into what has to be there.
+// So one select (Q: E_k = y_k) serves the bounce, R2 and R3.  The flips of
+// the three pairs add up to Q times the parity of the six channels, which
+// gives the third one from the other two.
+
+// E_k from d_k = Q & y_k and R1's select (r1) and pick (m_k): see above.
+FHP_HD uint32_t pair_flip(uint32_t d, uint32_t r1, uint32_t m) {
+    return lop3<(kA | (kB & ~kC)) & 0xFF>(d, r1, m);
+}
+
+// Class counts of the six moving channels: even class 2 ce + se, odd class
+// 2 co + so.
+struct ClassCounts {
+    uint32_t se, ce, so, co;
 };
 
-FHP_HD Counts counts(const uint32_t a[7]) {
-    Counts K;
-    K.se = xor3(a[0], a[2], a[4]);
-    K.ce = maj3(a[0], a[2], a[4]);
-    K.so = xor3(a[1], a[3], a[5]);
-    K.co = maj3(a[1], a[3], a[5]);
-    K.n0 = K.se ^ K.so;
-    const uint32_t c0 = K.se & K.so;
-    K.n1 = xor3(K.ce, K.co, c0);
-    K.n2 = maj3(K.ce, K.co, c0);
-    uint32_t pp = a[0] & a[3];
-    pp = lop3<kA | (kB & kC)>(pp, a[1], a[4]);
-    K.pp = lop3<kA | (kB & kC)>(pp, a[2], a[5]);
-    K.eq024 = lop3<(kA & kB & kC) | (~kA & ~kB & ~kC)>(a[0], a[2], a[4]);
-    return K;
+FHP_HD ClassCounts class_counts(const uint32_t a[7]) {
+    return {xor3(a[0], a[2], a[4]), maj3(a[0], a[2], a[4]), xor3(a[1], a[3], a[5]),
+            maj3(a[1], a[3], a[5])};
 }
 
-// Collision of 32 nodes after streaming (fluid nodes) and bounce-back (solid
-// nodes), FHP-II or FHP-I.  a[0..5] moving channels, a[6] rest, s solid, chi
-// chirality.
-//
-// Every colliding state maps each output channel j to a function of the two
-// channels next to it, A = a_{j-1} and B = a_{j+1} (indices mod 6):
-//   R1 head-on pair alone (rest particle a spectator): the pair turns by
-//      +60 deg (chi = 1) or -60 deg (chi = 0): o_j = chi ? A : B;
-//   R2 {0,2,4} <-> {1,3,5} (FHP-II: without rest particle): o_j = A (= B);
-//   R3 (FHP-II only) one particle c plus rest -> {c-1, c+1}: o_j = A | B,
-//      and {c-1, c+1} without rest -> c plus rest: o_j = A & B; i.e.
-//      o_j = maj(rest, A, B), and the rest bit flips.
-// Both forms are "A where A = B, else Z": Z = (chi XNOR A) for R1/R2 and
-// Z = rest for R3.  The rule that applies comes from the number of moving
-// particles: R1 = (n = 2) & (an opposite pair present); R3 = rest ? (n = 1) :
-// ((n = 2) & both particles in one class, i.e. at 120 deg); R2 = (n = 3),
-// channels 0, 2, 4 equal (and no rest for FHP-II).  The rule masks ignore
-// the solid bit: a solid node takes the bounced channel j+3 in the last
-// select whatever its rule mask says, and keeps its rest bit.
-template <int RULES>
-FHP_HD void collide_fhp12(const uint32_t a[7], const Counts& K, uint32_t s, uint32_t chi,
-                          uint32_t o[7]) {
-    const uint32_t r = a[6];
-    const uint32_t is2 = lop3<~kA & kB & ~kC>(K.n0, K.n1, K.n2);
-    const uint32_t is3 = K.n0 & K.n1;  // n = 7 cannot occur
-    uint32_t c12, c3, zc;
-    if constexpr (RULES == kRulesFHP1) {
-        const uint32_t tri = is3 & K.eq024;                                   // R2
-        c12 = lop3<((kA & kB) | kC) & 0xFF>(is2, K.pp, tri);                  // R1 or R2
-        c3 = 0;
-        zc = ~chi;
-    } else {
-        const uint32_t tri = lop3<kA & kB & ~kC>(is3, K.eq024, r);          // R2
-        c12 = lop3<((kA & kB) | kC) & 0xFF>(is2, K.pp, tri);                  // R1 or R2
-        const uint32_t is1 = lop3<kA & ~kB & ~kC>(K.n0, K.n1, K.n2);
-        const uint32_t f3 = is2 & ~K.se;                                      // two at 120 deg
-        c3 = lop3<(kA & kB) | (~kA & kC)>(r, is1, f3);                      // R3: r ? n = 1 : f3
-        zc = lop3<(kA & ~kB) | (~kA & kC)>(c12, chi, r);                    // c12 ? ~chi : r
-    }
-    const uint32_t any = c12 | c3;                                          // a rule applies
+// R1's select: one particle in each class (c1: its first part) and the two
+// opposite each other, which is a_0 = a_3 and a_2 = a_5.
+FHP_HD uint32_t opposite(uint32_t c1, const uint32_t a[7]) {
+    const uint32_t c2 = lop3<kA & ~(kB ^ kC)>(c1, a[0], a[3]);
+    return lop3<kA & ~(kB ^ kC)>(c2, a[2], a[5]);
+}
+
+// The pair flips of a[0..5] for selects q (Q) and r1, x = parity of the six.
+FHP_HD void pair_flips(const uint32_t a[7], uint32_t q, uint32_t r1, uint32_t x, uint32_t chi,
+                       uint32_t E[3]) {
+    const uint32_t d0 = lop3<kA & (kB ^ kC)>(q, a[0], a[3]);
+    const uint32_t d1 = lop3<kA & (kB ^ kC)>(q, a[1], a[4]);
+    E[0] = pair_flip(d0, r1, mux3(chi, a[1], a[2]));
+    E[1] = pair_flip(d1, r1, mux3(chi, a[2], a[0]));
+    E[2] = xor3(E[0], E[1], q & x);
+}
+
+// FHP-I: R1 and R2 whatever the rest particle, which never changes.
+// 26 operations.
+FHP_HD void collide_fhp1(const uint32_t a[7], uint32_t s, uint32_t chi, uint32_t o[7]) {
+    const ClassCounts n = class_counts(a);
+    const uint32_t x = n.se ^ n.so;
+    const uint32_t w = lop3<~(kA ^ kB) & (kA ^ kC)>(n.se, n.ce, n.so);  // e in {0, 3}, x
+    const uint32_t q = lop3<kA & ~(kB ^ kC)>(w, n.so, n.co) | s;        // and o in {0, 3}: R2
+    const uint32_t e1 = lop3<kA & ~kB & ~kC>(n.se, n.ce, s);            // e = 1, fluid
+    const uint32_t r1 = opposite(lop3<kA & kB & ~kC>(e1, n.so, n.co), a);
+    uint32_t E[3];
+    pair_flips(a, q, r1, x, chi, E);
 #pragma unroll
-    for (int j = 0; j < 6; j++) {
-        const uint32_t am = a[(j + 5) % 6], ap = a[(j + 1) % 6];
-        const uint32_t z = lop3<kA ^ (kB & kC)>(zc, c12, am);             // zc ^ (c12 & A)
-        const uint32_t sp = lop3<(((kA ^ kB) & kC) | (~(kA ^ kB) & kA)) & 0xFF>(am, ap, z);
-        const uint32_t fl = mux3(any, sp, a[j]);                           // fluid: collide or keep
-        o[j] = mux3(s, a[(j + 3) % 6], fl);                                // solid: bounce back
-    }
-    o[6] = lop3<kA ^ (kB & ~kC)>(r, c3, s);                               // r ^ (c3 & ~s)
+    for (int j = 0; j < 6; j++) o[j] = a[j] ^ E[j % 3];
+    o[6] = a[6];
 }
 
-// FHP-II collision of 32 nodes with the rule masks formed from the class
-// counts alone (19 operations where counts() + collide_fhp12 take 21).  With
-// e, o the particle counts of the even and odd class (se/ce, so/co their
-// parity and carry bits) and x = se ^ so (the total is odd):
-//   R1, a head-on pair alone: e = o = 1 and an opposite pair present;
-//   R2, three in one class without rest: e, o in {0, 3} and x (e != o);
-//   R3: with rest, one particle (x and no carry); without rest, two
-//       particles in one class (no parity bit, exactly one carry).
-// The per-channel outputs are those of collide_fhp12.
+// FHP-II: R1, R2 without rest particle, R3.  32 operations (44 when each
+// channel selects among its neighbours' values).  Te, To: one class is empty
+// and the other (even, odd) holds a colliding number: one particle with a
+// rest particle (R3), two (R3) or three (R2) without.  R2's total is odd and
+// has no rest particle, R3's parity equals the rest bit, so R3 on a fluid node
+// is T with x = rest.
 FHP_HD void collide_fhp2(const uint32_t a[7], uint32_t s, uint32_t chi, uint32_t o[7]) {
     const uint32_t r = a[6];
-    const uint32_t se = xor3(a[0], a[2], a[4]), ce = maj3(a[0], a[2], a[4]);
-    const uint32_t so = xor3(a[1], a[3], a[5]), co = maj3(a[1], a[3], a[5]);
-    const uint32_t x = se ^ so;
-    const uint32_t one = lop3<kA & ~kB & ~kC>(x, ce, co);          // one particle
-    const uint32_t two_cls = lop3<~kA & ~kB & kC>(se, so, ce ^ co);  // two in one class
-    const uint32_t c3 = mux3(r, one, two_cls);                       // R3
-    uint32_t pp = a[0] & a[3];
-    pp = lop3<kA | (kB & kC)>(pp, a[1], a[4]);
-    pp = lop3<kA | (kB & kC)>(pp, a[2], a[5]);                      // an opposite pair
-    const uint32_t e1o1 = lop3<kA & kB & ~kC>(se, so, ce);          // with ~co: e = o = 1
-    const uint32_t r1 = lop3<kA & ~kB & kC>(e1o1, co, pp);          // R1
-    const uint32_t w = lop3<kA & ~(kB ^ kC)>(x, se, ce);            // x, e in {0, 3}
-    const uint32_t r2 = lop3<kA & ~(kB ^ kC)>(w, so, co);           // and o in {0, 3}
-    const uint32_t c12 = lop3<kA | (kB & ~kC)>(r1, r2, r);          // R1 or R2 (no rest)
-    const uint32_t zc = lop3<(kA & ~kB) | (~kA & kC)>(c12, chi, r); // c12 ? ~chi : r
-    const uint32_t any = c12 | c3;
+    const ClassCounts n = class_counts(a);
+    const uint32_t x = n.se ^ n.so;
+    const uint32_t ue = lop3<(kC & kA & ~kB) | (~kC & kB)>(n.se, n.ce, r);  // r ? e = 1 : e >= 2
+    const uint32_t uo = lop3<(kC & kA & ~kB) | (~kC & kB)>(n.so, n.co, r);
+    const uint32_t te = lop3<kA & ~kB & ~kC>(ue, n.so, n.co);
+    const uint32_t to = lop3<kA & ~kB & ~kC>(uo, n.se, n.ce);
+    const uint32_t q = or3(te, to, s);
+    const uint32_t f = lop3<~(kA ^ kB) & ~kC>(x, r, s);
+    const uint32_t vo = te & f, ve = to & f;  // the empty class flips
+    const uint32_t e1 = lop3<kA & kB & ~kC>(n.se, n.so, n.ce);
+    // s takes the place of co, which the opposite pair implies: with a_0 = a_3
+    // and a_2 = a_5 the classes differ in channels 1 and 4 alone, and equal
+    // parities make those equal too
+    const uint32_t r1 = opposite(e1 & ~s, a);
+    uint32_t E[3];
+    pair_flips(a, q, r1, x, chi, E);
 #pragma unroll
-    for (int j = 0; j < 6; j++) {
-        const uint32_t am = a[(j + 5) % 6], ap = a[(j + 1) % 6];
-        const uint32_t z = lop3<kA ^ (kB & kC)>(zc, c12, am);
-        const uint32_t sp = lop3<(((kA ^ kB) & kC) | (~(kA ^ kB) & kA)) & 0xFF>(am, ap, z);
-        const uint32_t fl = mux3(any, sp, a[j]);
-        o[j] = mux3(s, a[(j + 3) % 6], fl);
-    }
-    o[6] = lop3<kA ^ (kB & ~kC)>(r, c3, s);
+    for (int j = 0; j < 6; j++) o[j] = xor3(a[j], E[j % 3], (j & 1) ? vo : ve);
+    o[6] = lop3<kA ^ (kB | kC)>(r, vo, ve);
 }
 
 // Collision-saturated FHP-III.  Nodes of mass >= 4 are handled through their
-// complement (particle-hole duality: T(s) = ~T(~s)), so the rules below act
-// on mass <= 3 only: FHP-II, plus for every spectator position j the cycle
+// complement b (particle-hole duality: T(s) = ~T(~s), so the flips of s are
+// those of ~s); the rules below therefore meet mass <= 3 only: FHP-II, R1 with
+// or without rest, plus for every spectator position j the cycle
 // A_j -> B_j -> C_j -> A_j (chi = 1; reversed for chi = 0) with
 //   A_j = {j, j+1, j+4}, B_j = {j, j+2, j+5}, C_j = {j+1, j+5} + rest.
-// Bounce-back commutes with the complement, so solid nodes need no care.
+// A_j and B_j are a head-on pair and a spectator: y_k is set for the
+// spectator's pair alone, and the pair is the next one (A) or the one before
+// (B).  The flips:
+//   A_j <-> B_j (select D): the pair turns, E_k = ~y_k;
+//   A_j, B_j -> C_j (select F): the class holding two empties, and the
+//     channel of the other class between those two flips;
+//   C_j -> A_j (chi = 1), B_j (chi = 0): in the empty class every channel
+//     whose neighbour at +1 (chi = 1) or -1 (chi = 0) is set flips, in the
+//     other the particle whose other one lies at +2 or -2.
+// F and C flip the rest particle.  Bounce-back flips commute with the
+// complement, so solid nodes need no care there.
 FHP_HD void collide_fhp3(const uint32_t a[7], uint32_t s, uint32_t chi, uint32_t o[7]) {
-    const Counts K0 = counts(a);
-    // mass = n + rest >= 4  <=>  n >= 4, or n = 3 with a rest particle
-    const uint32_t cm = lop3<(kA & kB & kC)>(K0.n0, K0.n1, a[6]) | K0.n2;
+    const ClassCounts n0 = class_counts(a);
+    const uint32_t x = n0.se ^ n0.so;  // the complement keeps the parity of six channels
+    const uint32_t c0 = n0.se & n0.so;
+    const uint32_t n1 = xor3(n0.ce, n0.co, c0), n2 = maj3(n0.ce, n0.co, c0);
+    // mass >= 4: four or more moving particles, or three with a rest particle
+    const uint32_t cm = lop3<(kA & kB & kC)>(x, n1, a[6]) | n2;
     uint32_t b[7];
 #pragma unroll
     for (int c = 0; c < 7; c++) b[c] = a[c] ^ cm;
-    // Counts of the complemented state from those of a: a class of three
-    // channels with e particles has 3 - e after the complement, which flips
-    // both bits of e (so the parity of the total is unchanged).
-    Counts K;
-    K.se = K0.se ^ cm;
-    K.ce = K0.ce ^ cm;
-    K.so = K0.so ^ cm;
-    K.co = K0.co ^ cm;
-    K.n0 = K0.n0;
-    const uint32_t c0 = K.se & K.so;
-    K.n1 = xor3(K.ce, K.co, c0);
-    K.n2 = maj3(K.ce, K.co, c0);
-    // head-on pairs (k, k+3) one by one: the three-cycles need them singly
-    const uint32_t P0 = b[0] & b[3], P1 = b[1] & b[4], P2 = b[2] & b[5];
-    K.pp = or3(P0, P1, P2);
-    K.eq024 = lop3<(kA & kB & kC) | (~kA & ~kB & ~kC)>(b[0], b[2], b[4]);
-    uint32_t ob[7];
-    collide_fhp12<kRulesFHP2>(b, K, s, chi, ob);
-    const uint32_t rb = b[6];
-    const uint32_t is3 = K.n0 & K.n1;
-    const uint32_t is2 = lop3<~kA & kB & ~kC>(K.n0, K.n1, K.n2);
-    // three moving with a head-on pair, no rest; two at 120 deg plus rest
-    const uint32_t p3 = lop3<kA & ~kB & ~kC>(is3 & K.pp, rb, s);
-    const uint32_t p2 = lop3<kA & ~kB & kC>(is2, K.se, rb) & ~s;
-    // A_j holds the pair (j+1, j+4) and B_j the pair (j+2, j+5), each with
-    // particle j: q[k] marks the p3 nodes whose pair is (k, k+3)
-    const uint32_t q[3] = {p3 & P0, p3 & P1, p3 & P2};
-    // Results of the cycles, gathered per channel: channel c collects A_c,
-    // A_{c-1}, A_{c+2}, B_c, B_{c-2}, B_{c+1}, C_{c-1}, C_{c+1}; the rest bit
-    // every C.  A_j and B_{j+2} both add to channel j+4, so each A_j waits two
-    // steps for its partner; the C_j pair up for the rest bit.
-    uint32_t nw[7] = {0, 0, 0, 0, 0, 0, 0};
-    uint32_t tA_hold[6] = {0, 0, 0, 0, 0, 0};
-    uint32_t tC_prev = 0;
+    const uint32_t r = b[6];
+    // a class of three channels with e particles has 3 - e after the
+    // complement, which flips both bits of e
+    const uint32_t se = n0.se ^ cm, ce = n0.ce ^ cm, so = n0.so ^ cm, co = n0.co ^ cm;
+    // at most three particles: two or three in one class (ce, co exclude each
+    // other); with a rest particle at most two move
+    const uint32_t two = ce | co;
+    const uint32_t r3 = lop3<(kA & kB) | (~kA & ~kB & kC)>(r, x, two);
+    const uint32_t r3f = r3 & ~s;
+    const uint32_t vo = lop3<kA & (kB | kC)>(r3f, se, ce);  // the empty class flips
+    const uint32_t ve = lop3<kA & (kB | kC)>(r3f, so, co);
+    const uint32_t C = lop3<kA & kB & ~kC>(r, two, s);
+    const uint32_t xf = x & ~s;
+    const uint32_t z = lop3<kA & ~(kB ^ kC)>(xf, ce, se);
+    const uint32_t q = or3(z & two, r3, s);  // z & two: R2
+    const uint32_t y0 = b[0] ^ b[3], y1 = b[1] ^ b[4];
+    const uint32_t p21 = lop3<kA & kB & ~kC>(xf, two, z);   // two and one
+    const uint32_t p3 = lop3<kA & ~(kB & kC)>(p21, y0, y1);  // with a head-on pair
+    const uint32_t isA = mux3(y0, b[1], mux3(y1, b[2], b[0]));
+    const uint32_t D = lop3<kA & ~(kB ^ kC)>(p3, isA, chi);
+    const uint32_t F = p3 & ~D;
+    const uint32_t r1 = opposite(lop3<kA & kB & ~kC>(se, so, s), b);
+    uint32_t E[3];
+    E[0] = pair_flip(mux3(y0, q, D), r1, mux3(chi, b[1], b[2]));
+    E[1] = pair_flip(mux3(y1, q, D), r1, mux3(chi, b[2], b[0]));
+    E[2] = xor3(E[0], E[1], q & x);
+    // F and C: the class holding two (even: ge, odd: go); h1, h0 pick C's side.
+    // With two of three channels p, q', c of a class set, c is ~(p & q').
+    const uint32_t g = F | C;
+    const uint32_t h1 = C & chi, h0 = C & ~chi;
+    const uint32_t g2[2] = {g & ce, g & co};
 #pragma unroll
     for (int j = 0; j < 6; j++) {
-        const int j1 = (j + 1) % 6, j2 = (j + 2) % 6, j5 = (j + 5) % 6;
-        const uint32_t iA = q[(j + 1) % 3] & b[j];
-        const uint32_t iB = q[(j + 2) % 3] & b[j];
-        const uint32_t iC = lop3<kA & kB & kC>(p2, b[j1], b[j5]);
-        const uint32_t tA = mux3(chi, iC, iB);  // nodes whose result is A_j = {j, j+1, j+4}
-        const uint32_t tB = mux3(chi, iA, iC);  // B_j = {j, j+2, j+5}
-        const uint32_t tC = mux3(chi, iB, iA);  // C_j = {j+1, j+5} + rest
-        nw[j] = or3(nw[j], tA, tB);
-        nw[j1] = or3(nw[j1], tA, tC);
-        nw[j5] = or3(nw[j5], tB, tC);
-        tA_hold[j] = tA;
-        // channel j+2 = (j-2)+4: A_{j-2} with B_j (A_{j-2} of j < 2 waits for the wrap)
-        if (j >= 2) nw[j2] = or3(nw[j2], tA_hold[j - 2], tB);
-        else nw[j2] |= tB;
-        if (j & 1) nw[6] = or3(nw[6], tC_prev, tC);
-        else tC_prev = tC;
+        const uint32_t gs = g2[j & 1], gn = g2[1 - (j & 1)];
+        const uint32_t am = b[(j + 5) % 6], ap = b[(j + 1) % 6];
+        const uint32_t p2 = b[(j + 2) % 6], m2 = b[(j + 4) % 6];
+        // two in the other class: F: A & B, C: chi ? B : A
+        const uint32_t u = lop3<(kA | kB) & kC>(am, h1, gn);
+        const uint32_t wn = lop3<kA & (kB | kC)>(u, ap, h0);
+        // two in this class: F: its particles, C: chi ? ~m2 : ~p2 -- of the
+        // two terms at most one is set
+        const uint32_t t1 = lop3<~kA & ~kB & kC & 0xFF>(p2, h1, gs);
+        const uint32_t t0 = lop3<~kA & ~kB & kC & 0xFF>(m2, h0, gs);
+        o[j] = xor3(xor3(a[j], E[j % 3], (j & 1) ? vo : ve), wn, t1 ^ t0);
     }
-    // A_4 and A_5 add to channels 2 and 3
-    nw[2] |= tA_hold[4];
-    nw[3] |= tA_hold[5];
-    const uint32_t cyc = p3 | p2;
-#pragma unroll
-    for (int k = 0; k < 7; k++) o[k] = lop3<(kA & ~kB) | kC>(ob[k], cyc, nw[k]) ^ cm;
+    o[6] = a[6] ^ or3(r3f, F, C);
 }
 
 // Update of 32 nodes after streaming: collision (fluid) or bounce-back
@@ -266,7 +255,7 @@ FHP_HD void update32(const uint32_t a[7], uint32_t s, uint32_t chi, uint32_t coi
     } else if constexpr (RULES == kRulesFHP2) {
         collide_fhp2(a, s, chi, o);
     } else {
-        collide_fhp12<RULES>(a, counts(a), s, chi, o);
+        collide_fhp1(a, s, chi, o);
     }
     const uint32_t cf = lop3<kA & ~kB & kC>(coin, s, up);
     const uint32_t o5 = lop3<kA & ~(kB & ~kC)>(o[5], cf, o[2]);
