@@ -173,6 +173,15 @@ uint32_t default_depth(uint32_t H, uint32_t wd, uint32_t simds) {
     return T <= 8 ? 4 : FHP_MAX_DEPTH;
 }
 
+// Tiles against sweeping bands (default depth and band): lattices of up to
+// kTileNodes nodes run tiled passes.
+TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) {
+    constexpr uint64_t kTileNodes = 8192ull * 9216;
+    if (n < 2 || (uint64_t)L.W * L.H > kTileNodes) return TilePlan{};
+    const double alu = D.rules == FHP_RULES_FHP3 ? 1.6 : 1.0;
+    return tile_plan(L.H, L.wd, simds / 4, D.thr_force ? alu : alu - 0.2, n);
+}
+
 Dyn dyn_for(const fhp_params* p) {
     Dyn D;
     D.key_chir = hash64(p->seed, kTagChir);
@@ -219,7 +228,9 @@ int sim_setup(fhp_sim* s, const fhp_params* p, uint64_t* planes, const Layout& l
     s->D = dyn_for(p);
     s->simds = device_simds();
     s->depth = default_depth(s->L.H, s->L.wd, s->simds);
+    s->own_depth = false;
     s->band = 0;
+    s->plan_n = 0;
 
     FHP_HIP_TRY(launch_fill_u64(s->S, lay.plane_words, 0, st), "clear solid plane");
     s->has_mask = 0;
@@ -280,6 +291,7 @@ int fhp_set_depth(fhp_sim* s, uint32_t k) {
     if (k > 1 && s->L.wd > kMaxBlockedWords)
         return fail(FHP_E_INVAL, "depth %u needs width <= %u", k, 64 * kMaxBlockedWords);
     s->depth = k ? k : default_depth(s->L.H, s->L.wd, s->simds);
+    s->own_depth = k != 0;
     return FHP_OK;
 }
 
@@ -309,6 +321,22 @@ int fhp_step(fhp_sim* s, uint64_t n) {
                     (unsigned long long)s->t, (unsigned long long)n);
     if (s->changed && n) *s->changed = 1;
     const Lattice L = lattice_of(s);
+    if (!s->own_depth && !s->band && n > 1) {
+        if (s->plan_n != n) {
+            s->plan = plan_tiles(L, s->D, s->simds, n);
+            s->plan_n = n;
+        }
+        // as many launches as the deepest ones take, evenly deep
+        for (uint64_t left = s->plan.R ? (n + s->plan.n - 1) / s->plan.n : 0; left > 0; left--) {
+            const uint32_t k = (uint32_t)((n + left - 1) / left);
+            if (fault_launch()) return hip_fail(hipErrorLaunchFailure, "step (injected by FHP_FAULT)");
+            FHP_HIP_TRY(launch_tile(s->plan, k, s->buf[s->cur], s->buf[1 - s->cur], L, s->D, s->t, s->st),
+                        "step");
+            s->cur ^= 1;
+            s->t += k;
+            n -= k;
+        }
+    }
     uint32_t depth = s->depth;
     if (s->D.rules == FHP_RULES_FHP3 && depth > kMaxDepthFHP3) depth = kMaxDepthFHP3;
     const uint32_t T = s->band ? s->band : default_band(s->L.H, s->L.wd, s->simds);

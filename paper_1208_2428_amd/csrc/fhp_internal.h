@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/fhp.h"
+#include "fhp_tile_plan.h"
 
 namespace fhp {
 
@@ -95,6 +96,12 @@ hipError_t launch_step1(const uint64_t* in, uint64_t* out, const Lattice& L, con
 // on a device of `simds` SIMDs.  Needs L.wd <= kMaxBlockedWords.
 hipError_t launch_stepk(uint32_t K, const uint64_t* in, uint64_t* out, const Lattice& L,
                         const Dyn& D, uint64_t t, uint32_t T, uint32_t simds, hipStream_t st);
+// `steps` (at most P.n) steps in one tiled pass (fhp_tile1.hip).
+hipError_t launch_tile(const TilePlan& P, uint32_t steps, const uint64_t* in, uint64_t* out,
+                       const Lattice& L, const Dyn& D, uint64_t t, hipStream_t st);
+// The tiled passes for n steps of a lattice, or no plan (R = 0) where
+// sweeping bands are faster.
+TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n);
 
 }  // namespace fhp
 
@@ -112,7 +119,10 @@ struct fhp_sim {
     int cur;         // buffer holding the current state
     uint64_t t;      // steps completed
     uint32_t depth;  // temporal-block depth K
+    bool own_depth;  // depth was set by the caller: passes of exactly that depth
     uint32_t band;   // rows per workgroup of the blocked kernel (0 = default)
+    fhp::TilePlan plan;  // tiled passes for calls of plan_n steps (0: none yet)
+    uint64_t plan_n;
     uint32_t simds;  // SIMDs of the device the simulation runs on (4 per CU)
     int has_mask;
     hipStream_t st;

@@ -97,14 +97,17 @@ extern "C" int fhp_step_noalloc(const fhp_params* p, const uint64_t* dev_in, uin
     uint32_t K = depth ? depth : default_depth(L.H, wd, simds);
     if (D.rules == FHP_RULES_FHP3 && K > kMaxDepthFHP3) K = kMaxDepthFHP3;
     const uint32_t T = default_band(L.H, wd, simds);
-    // Passes of K steps (the last one shorter), alternating between dev_out
+    // Tiled passes, evenly deep, or passes of K steps (the last one shorter), alternating between dev_out
     // and the scratch buffer so that the last pass writes dev_out.
-    uint64_t passes = (n + K - 1) / K;
+    const TilePlan plan = depth ? TilePlan{} : plan_tiles(L, D, simds, n);
+    uint64_t passes = plan.R ? (n + plan.n - 1) / plan.n : (n + K - 1) / K;
     const uint64_t* src = dev_in;
     while (n > 0) {
-        const uint32_t k = n >= K ? K : (uint32_t)n;
+        const uint32_t k = plan.R ? (uint32_t)((n + passes - 1) / passes) : n >= K ? K : (uint32_t)n;
         uint64_t* dst = (passes % 2 == 1) ? dev_out : mid;
-        if (k == 1)
+        if (plan.R)
+            FHP_HIP_TRY(launch_tile(plan, k, src, dst, L, D, t, st), "step");
+        else if (k == 1)
             FHP_HIP_TRY(launch_step1(src, dst, L, D, t, st), "step");
         else
             FHP_HIP_TRY(launch_stepk(k, src, dst, L, D, t, T, simds, st), "step");
