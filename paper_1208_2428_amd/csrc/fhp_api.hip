@@ -178,8 +178,7 @@ uint32_t default_depth(uint32_t H, uint32_t wd, uint32_t simds) {
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) {
     constexpr uint64_t kTileNodes = 8192ull * 9216;
     if (n < 2 || (uint64_t)L.W * L.H > kTileNodes) return TilePlan{};
-    const double alu = D.rules == FHP_RULES_FHP3 ? 1.6 : 1.0;
-    return tile_plan(L.H, L.wd, simds / 4, D.thr_force ? alu : alu - 0.2, n);
+    return tile_plan(L.H, L.wd, simds / 4, D.rules == FHP_RULES_FHP3, D.thr_force != 0, n);
 }
 
 Dyn dyn_for(const fhp_params* p) {

@@ -94,21 +94,29 @@ __device__ __forceinline__ bool tile_stores(const TileArgs& a, const TilePlace& 
            (p.full || p.tx * a.out_words + oc < a.wd);
 }
 
-// True when no row of the wave matters to the tile's own rows after step st.
-__device__ __forceinline__ bool tile_idle(const TileArgs& a, const TilePlace& p, uint32_t st) {
-    const uint32_t reach = a.steps - 1 - st;
-    return p.row_hi + reach < a.halo || p.row_lo >= a.halo + a.T + reach;
+// Steps that the wave takes part in: step st matters to the tile's own rows
+// only within steps - 1 - st rows of them.
+__device__ __forceinline__ uint32_t tile_live_steps(const TileArgs& a, const TilePlace& p) {
+    const uint32_t below = a.halo > p.row_hi ? a.halo - p.row_hi : 0;
+    const uint32_t last = a.halo + a.T - 1;
+    const uint32_t above = p.row_lo > last ? p.row_lo - last : 0;
+    const uint32_t off = max(below, above);
+    return off < a.steps ? a.steps - off : 0;
 }
 
-// Runs step(st, slot to read, slot to write) for every step.
+// Runs step(slot to read, slot to write) for every step that the wave takes
+// part in; it keeps the barriers of the others.  (Skipping inside the step
+// cost 30 registers: the state then flows through both branches.)
 template <class Slot, class F>
-__device__ __forceinline__ void tile_loop(uint32_t steps, Slot* slots, F&& step) {
+__device__ __forceinline__ void tile_loop(const TileArgs& a, const TilePlace& p, Slot* slots, F&& step) {
+    const uint32_t live = tile_live_steps(a, p);
     uint32_t st = 0;
-    for (; st + 2 <= steps; st += 2) {
-        step(st, slots[0], slots[1]);
-        step(st + 1, slots[1], slots[0]);
+    for (; st + 2 <= live; st += 2) {
+        step(slots[0], slots[1]);
+        step(slots[1], slots[0]);
     }
-    if (st < steps) step(st, slots[0], slots[1]);
+    if (st < live) step(slots[0], slots[1]);
+    for (st = live; st < a.steps; st++) lds_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -150,13 +158,9 @@ __device__ __forceinline__ void tile1_steps(WordSlot<NT>* slots, const TileArgs&
         L.l5[me] = lo32(p[5]);
     };
     put(slots[0]);
-    tile_loop(a.steps, slots, [&](uint32_t st, WordSlot<NT>& L, WordSlot<NT>& next) __attribute__((always_inline)) {
+    tile_loop(a, at, slots, [&](WordSlot<NT>& L, WordSlot<NT>& next) __attribute__((always_inline)) {
         const uint64_t R = in_sgprs(tq);
         tq += t_step;
-        if (tile_idle(a, at, st)) {
-            lds_barrier();
-            return;
-        }
         // One hash covers the writes' latency before the barrier, the other
         // the reads' after it.
         const uint64_t chi = chir_word(mix64(base_chi + R), chi_and, a.chi_or);
@@ -226,14 +230,14 @@ struct PairSlot {
 };
 
 // Waves per SIMD the compiler is to make room for.
-template <int NT>
+template <int RULES>
 constexpr int pair_waves() {
-    return NT == 640 ? 5 : 4;
+    return RULES == kRulesFHP3 ? 4 : 5;
 }
 
 // SOLID: the lattice has obstacles or walls.
 template <int NT, bool FORCE, bool SOLID, int RULES>
-__global__ void __launch_bounds__(NT, pair_waves<NT>()) k_tile2(const uint64_t* __restrict__ in,
+__global__ void __launch_bounds__(NT, pair_waves<RULES>()) k_tile2(const uint64_t* __restrict__ in,
                                                                 uint64_t* __restrict__ out,
                                                                 const uint64_t* __restrict__ S,
                                                                 TileArgs a) {
@@ -278,13 +282,9 @@ __global__ void __launch_bounds__(NT, pair_waves<NT>()) k_tile2(const uint64_t* 
         L.e4[me] = lo32(pe[4]);
     };
     put(slots[0]);
-    tile_loop(a.steps, slots, [&](uint32_t st, PairSlot<NT>& L, PairSlot<NT>& next) __attribute__((always_inline)) {
+    tile_loop(a, at, slots, [&](PairSlot<NT>& L, PairSlot<NT>& next) __attribute__((always_inline)) {
         const uint64_t Re = in_sgprs(tq), Ro = in_sgprs(tq + row_step);
         tq += t_step;
-        if (tile_idle(a, at, st)) {
-            lds_barrier();
-            return;
-        }
         uint64_t coine = 0, coino = 0;
         uint32_t upe = 0, upo = 0;
         auto force = [&](uint64_t R, uint64_t& coin, uint32_t& upm) __attribute__((always_inline)) {

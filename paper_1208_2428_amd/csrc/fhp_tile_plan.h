@@ -8,10 +8,12 @@
 // the cheapest shape under a model of a launch's time,
 //   A + rounds B + n (rounds L + work c)  microseconds,
 // rounds = workgroups a compute unit runs one after the other, work = rows of
-// 64 words a SIMD updates per step.  Its constants are fitted to 1000 measured
-// launches of 23 lattices from 64^2 to 12288 x 8192 (model over measured 0.85
-// to 1.14 for 80% of them); over those lattices the shape it picks is within
-// 7% of the fastest one measured, 1% in the median.
+// 64 words a SIMD updates per step.  Its constants are fitted to 900 measured
+// launches of 20 lattices from 64^2 to 16384^2 (model over measured 0.85 to
+// 1.15 for 80% of them).  Over those lattices the shape it picks is within 10%
+// of the fastest one measured, 1% in the median: 256^2 0.54 us per step (the
+// fastest 0.53), 1024^2 0.75 (0.74), 2048^2 1.04 (1.04), 4096^2 2.20 (2.11),
+// 8192 x 8128 8.3 (7.5).
 #pragma once
 
 #include <stdint.h>
@@ -21,9 +23,7 @@
 namespace fhp {
 
 constexpr uint32_t kTileMaxSteps = 32;  // deepest tiled launch
-// Workgroup sizes (threads) of the kernels with one and two rows per thread.
-constexpr uint32_t kTileThreads1[] = {256, 512, 1024};
-constexpr uint32_t kTileThreads2[] = {320, 512, 640, 1024};
+constexpr uint32_t kTileMaxThreads = 1024;
 
 struct TilePlan {
     uint32_t R;  // rows per thread (0: no plan)
@@ -48,9 +48,16 @@ inline uint32_t tiles_per_row(uint32_t C, uint32_t wd) {
     return (wd + o - 1) / o;
 }
 
+// Model constants by rows per thread: FHP-I and FHP-II with forcing, FHP-III.
+struct TileModel {
+    double A, B, L, c;
+};
+constexpr TileModel kTileModel[2][2] = {{{0.0, 7.7, 0.0, 0.33}, {1.9, 8.2, 0.0, 0.266}},
+                                        {{4.8, 4.1, 0.07, 0.55}, {0.4, 9.5, 0.62, 0.40}}};
+
 // The cheapest shape for `steps` steps of an H x wd-word lattice on `cus`
-// compute units; alu scales the arithmetic (1 = FHP-II with forcing).
-inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, double alu, uint64_t steps) {
+// compute units.  Without forcing a step has 0.8 times the arithmetic.
+inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool force, uint64_t steps) {
     TilePlan best{};
     auto consider = [&](uint32_t R, uint32_t C, uint32_t threads, uint32_t n) {
         const uint32_t halo = tile_halo(n);
@@ -62,20 +69,21 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, double alu, uin
         T = ((H + ty - 1) / ty + 1) & ~1u;  // the same number of tiles, even ones
         const uint32_t rows = T + 2 * halo, waves = tile_threads(R, rows, C) / 64;
         const uint64_t grid = (uint64_t)ty * tiles_per_row(C, wd);
-        // workgroups a compute unit holds: by registers 24 waves (R = 2: 20),
-        // by its 160 KB of LDS 2 for the kernels of 1024 (R = 1) or 512 and
-        // 640 threads (R = 2) and 1 for 1024 (R = 2)
+        // workgroups a compute unit holds: by registers 24 waves (R = 2 and
+        // FHP-III: 20 and 16), by its 160 KB of LDS 80 bytes (R = 2: 112) per
+        // thread of the kernel's size
         const uint32_t lds = R == 1 ? (threads <= 256 ? 8 : threads <= 512 ? 4 : 2)
                                     : (threads <= 320 ? 4 : threads <= 640 ? 2 : 1);
-        const uint32_t held = std::max(1u, std::min(lds, (R == 1 ? 24u : 20u) / waves));
+        const uint32_t regs = (fhp3 ? 16u : R == 1 ? 24u : 20u) / waves;
+        const uint32_t held = std::max(1u, std::min(lds, regs));
         const uint64_t per_cu = (grid + cus - 1) / cus;
         const double rounds = (double)((per_cu + held - 1) / held);
         // rows beyond those that still matter are skipped wave by wave
         const double live = std::min(1.0, (double)(T + n - 1 + R) / rows);
-        double work = per_cu * waves * live * R / 4.0;
-        if (per_cu == 1) work = std::max(work, (double)R);
-        const double launch = R == 1 ? 1.8 + 2.6 * rounds : 7.0 * rounds;
-        const double step = R == 1 ? work * 0.36 * alu : 0.05 * rounds + work * 0.26 * alu;
+        const double work = std::max(live * ((per_cu * waves + 3) / 4), 1.0) * R;
+        const TileModel& m = kTileModel[fhp3][R - 1];
+        const double launch = m.A + m.B * rounds;
+        const double step = m.L * rounds + work * m.c * (force ? 1.0 : 0.8);
         const uint64_t launches = (steps + n - 1) / n;
         const double us = launches * launch + (double)steps * step;
         if (best.R == 0 || us < best.us) {
@@ -86,8 +94,8 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, double alu, uin
             best.us = us;
         }
     };
-    const uint32_t depths[] = {8, 12, 16, 24, kTileMaxSteps};
-    const uint32_t widths[] = {6, 8, 10, 13, 18, 24, 34, 0};  // 0: full rows
+    const uint32_t depths[] = {8, 12, 16, 20, 24, 28, kTileMaxSteps};
+    const uint32_t widths[] = {5, 6, 8, 10, 13, 15, 18, 24, 34, 0};  // 0: full rows
     uint32_t last_n = 0;
     for (uint32_t n : depths) {
         n = (uint32_t)std::min<uint64_t>(n, steps);
@@ -101,9 +109,8 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, double alu, uin
             const uint32_t C = w ? (wd + k - 1) / k + 2 : wd;
             if (C == last_C || (w && C >= wd)) continue;
             last_C = C;
-            for (uint32_t t : kTileThreads1) consider(1, C, t, n);
-            consider(1, C, 768, n);
-            for (uint32_t t : kTileThreads2) consider(2, C, t, n);
+            for (uint32_t t : {256u, 384u, 512u, 640u, 768u, 1024u}) consider(1, C, t, n);
+            for (uint32_t t : {320u, 512u, 640u, 768u, 1024u}) consider(2, C, t, n);
         }
     }
     return best;
