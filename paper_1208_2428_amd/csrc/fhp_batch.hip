@@ -35,6 +35,7 @@
 #include "fhp_groups.h"
 #include "fhp_internal.h"
 #include "fhp_sweep.h"
+#include "fhp_tile.h"
 
 namespace fhp {
 namespace {
@@ -538,6 +539,10 @@ struct Engine {
     uint32_t depth_req = kBatchDefaultDepth;  // depth asked for; depth = its effective value
     uint32_t rules = FHP_RULES_FHP2;          // rule set of every member
     int use_graph = 1;
+    // tiled launches instead of sweeping bands (see engine_tiles)
+    bool tiles = false;
+    uint32_t tile_items = 0, tile_n = 0;      // tiles; most steps per launch
+    uint32_t tile_done = 0, tile_launches = 0;  // steps and launches since the tables were built
     // current tables
     uint32_t nt = 64, n_groups = 0, n_done = 0, n_members = 0;
     bool force = false, mask = false;
@@ -582,6 +587,9 @@ int engine_init(Engine* e, uint64_t* tables, uint32_t members, uint32_t segs, hi
     FHP_HIP_TRY(hipHostMalloc((void**)&e->stage, e->stage_bytes, hipHostMallocDefault), "pinned");
     FHP_HIP_TRY(hipEventCreateWithFlags(&e->staged, hipEventDisableTiming), "event");
     FHP_HIP_TRY(launch_fill_u64((uint64_t*)e->done, (segs + 1) / 2, 0, st), "clear");
+    // engine_status reads the header also where only tiled launches ran
+    static_assert(sizeof(BatchHeader) % sizeof(uint64_t) == 0, "the header is cleared in words");
+    FHP_HIP_TRY(launch_fill_u64((uint64_t*)e->hdr, sizeof(BatchHeader) / sizeof(uint64_t), 0, st), "clear");
     return FHP_OK;
 }
 
@@ -687,6 +695,91 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
     e->n_members = n;
     e->force = force;
     e->mask = mask;
+    return FHP_OK;
+}
+
+// Members of a tiled launch and the tiles of their shapes, in the tables'
+// memory (the band tables' place).
+static_assert(sizeof(TileMember) <= sizeof(MemberDesc), "tile members use the member table's memory");
+static_assert(sizeof(TileItem) <= sizeof(GroupDesc), "tiles use the group and wave tables' memory");
+
+// Tiles against bands.  A sweep pass has two waves per SIMD only from about
+// kTileBatchWords words on; below, its launches wait for their level chains,
+// and tiles step faster whatever the members' sizes.
+constexpr uint64_t kTileBatchWords = 1600000;
+
+// Decides between tiles and bands for sims[0..n) and calls of `steps` steps
+// (n_max: most steps per launch) and, for tiles, builds and uploads the tables.
+// limit: steps each may still run, or nullptr.  Leaves e->tiles.
+int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_t n, uint32_t n_max) {
+    e->tiles = false;
+    if (n == 0 || n > e->max_members) return FHP_OK;
+    uint64_t words = 0;
+    for (uint32_t i = 0; i < n; i++) words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
+    if (words > kTileBatchWords) return FHP_OK;
+    std::vector<TileShape> shapes(n);
+    uint64_t items = 0;
+    for (uint32_t i = 0; i < n; i++) {
+        shapes[i] = tile_shape(sims[i]->L.H, sims[i]->L.wd, n_max);
+        if (!shapes[i].T) return FHP_OK;
+        items += shapes[i].tiles;
+    }
+    // capacity of the group and wave tables (engine_table_words)
+    const uint64_t room = ((uint64_t)e->max_segs * sizeof(GroupDesc) + max_waves(e->max_segs) * sizeof(WaveDesc)) /
+                          sizeof(TileItem);
+    if (items > room || items > 0x7fffffffull) return FHP_OK;
+    FHP_HIP_TRY(hipEventSynchronize(e->staged), "event");
+    TileMember* M = (TileMember*)e->stage;
+    const size_t bm = (size_t)n * sizeof(TileMember), bi = (size_t)items * sizeof(TileItem);
+    if (bm + bi > e->stage_bytes) return FHP_OK;
+    TileItem* it = (TileItem*)(e->stage + bm);
+    bool force = false, solid = false;
+    for (uint32_t i = 0; i < n; i++) {
+        const fhp_sim* s = sims[i];
+        TileMember& m = M[i];
+        m.buf[0] = s->buf[0];
+        m.buf[1] = s->buf[1];
+        m.S = s->has_mask ? s->S : nullptr;
+        m.ps = s->L.ps;
+        m.t0 = s->t;
+        m.key_chir = s->D.key_chir;
+        m.key_force = s->D.key_force;
+        m.thr_force = (uint32_t)s->D.thr_force;
+        m.chi_and = (s->D.chir_mode == FHP_CHIR_HASH) ? ~0u : 0u;
+        m.chi_or = (s->D.chir_mode == FHP_CHIR_ONE) ? ~0u : 0u;
+        m.H = s->L.H;
+        m.wd = s->L.wd;
+        m.walls = s->L.walls;
+        m.cur = (uint32_t)s->cur;
+        m.steps = limit ? (uint32_t)limit[i] : kNoStepLimit;
+        m.T = shapes[i].T;
+        m.C = shapes[i].C;
+        m.out_words = tile_out_words(m.C, m.wd);
+        m.tiles_x = tiles_per_row(m.C, m.wd);
+        for (uint32_t k = 0; k < shapes[i].tiles; k++) *it++ = {i, k};
+        force |= s->D.thr_force != 0;
+        solid |= s->has_mask || s->L.walls;
+    }
+    FHP_HIP_TRY(hipMemcpyAsync(e->members, M, bm, hipMemcpyHostToDevice, e->st), "upload");
+    FHP_HIP_TRY(hipMemcpyAsync(e->groups, e->stage + bm, bi, hipMemcpyHostToDevice, e->st), "upload");
+    FHP_HIP_TRY(hipEventRecord(e->staged, e->st), "event");
+    e->tiles = true;
+    e->tile_items = (uint32_t)items;
+    e->tile_n = n_max;
+    e->tile_done = e->tile_launches = 0;
+    e->force = force;
+    e->mask = solid;
+    return FHP_OK;
+}
+
+// One tiled launch of n steps (members with at most n + tail steps left: all
+// of them).
+int engine_tile_launch(Engine* e, uint32_t n, uint32_t tail) {
+    FHP_HIP_TRY(launch_tile_items(e->tile_items, e->force, e->mask, e->rules, (const TileMember*)e->members,
+                                  (const TileItem*)e->groups, e->tile_done, e->tile_launches, n, tail, e->st),
+                "tiles");
+    e->tile_done += n;
+    e->tile_launches++;
     return FHP_OK;
 }
 
@@ -844,6 +937,7 @@ struct fhp_batch {
     uint64_t* aux;
     Engine eng;
     bool tables_dirty;  // tiling changed: rebuild before the next step
+    bool own_tiling;    // the caller chose the tiling: sweeping bands
     int changed;        // set by member handles when a member is changed alone
 };
 
@@ -865,6 +959,7 @@ struct fhp_pool {
     std::vector<PoolSlot> slots;
     std::vector<uint32_t> finished;  // done slots not yet reported
     uint32_t max_bands, bands_used;
+    bool own_band = false;  // the caller chose the bands' height: sweeping bands
     int changed;         // membership or a member changed: rebuild the tables
     std::vector<uint32_t> table_slots;  // slots in the current tables
 };
@@ -913,6 +1008,36 @@ int batch_rebuild(fhp_batch* b) {
     if (rc) return rc;
     b->tables_dirty = false;
     b->changed = 0;
+    return FHP_OK;
+}
+
+// n steps of every member in tiled launches, where the batch takes them
+// (eng.tiles).  The launches are evenly deep, at most kBatchTileSteps steps.
+constexpr uint32_t kBatchTileSteps = 16;
+int batch_step_tiles(fhp_batch* b, uint64_t n) {
+    Engine* e = &b->eng;
+    const uint64_t launches = (n + kBatchTileSteps - 1) / kBatchTileSteps;
+    const uint32_t deepest = (uint32_t)((n + launches - 1) / launches);
+    // the tables hold while nobody else steps the members and their step
+    // counter has room
+    if (!e->tiles || b->changed || e->tile_n < deepest || e->tile_done + n >= kTimeLimit) {
+        int rc = engine_tiles(e, b->ptrs.data(), nullptr, b->n, deepest);
+        if (rc) return rc;
+        b->tables_dirty = true;  // the band tables are gone
+        b->changed = 0;
+        if (!e->tiles) return FHP_OK;
+    }
+    uint64_t rest = n;
+    for (uint64_t left = launches; left > 0; left--) {
+        const uint32_t k = (uint32_t)((rest + left - 1) / left);
+        int rc = engine_tile_launch(e, k, 0);
+        if (rc) return rc;
+        for (uint32_t i = 0; i < b->n; i++) {
+            b->sims[i].t += k;
+            b->sims[i].cur ^= 1;
+        }
+        rest -= k;
+    }
     return FHP_OK;
 }
 
@@ -1001,6 +1126,7 @@ int fhp_batch_set_tiling(fhp_batch* b, uint32_t depth, uint32_t band, uint32_t g
     b->eng.band = band ? band : batch_default_band(b->sims, b->n, b->eng.depth);
     b->eng.nt_req = group_threads;
     b->eng.passes_per_launch = passes_per_launch;
+    b->own_tiling = depth || band || group_threads || passes_per_launch != 1;
     return batch_rebuild(b);
 }
 
@@ -1015,6 +1141,11 @@ int fhp_batch_step(fhp_batch* b, uint64_t n) {
     for (uint32_t i = 0; i < b->n; i++)
         if (b->sims[i].t + n >= kTimeLimit)
             return fail(FHP_E_STATE, "member %u: time would reach 2^24", i);
+    if (!b->own_tiling && n) {
+        int rc = batch_step_tiles(b, n);
+        if (rc) return rc;
+        if (b->eng.tiles) return FHP_OK;
+    }
     if (b->tables_dirty || b->changed) {
         int rc = batch_rebuild(b);
         if (rc) return rc;
@@ -1101,6 +1232,7 @@ int fhp_pool_set_tiling(fhp_pool* pl, uint32_t depth, uint32_t band, uint32_t gr
     pl->eng.depth_req = depth ? depth : kBatchDefaultDepth;
     pl->eng.depth = effective_depth(pl->eng.depth_req, pl->eng.rules);
     pl->eng.band = band ? band : 32;
+    pl->own_band = band != 0;
     pl->eng.nt_req = group_threads;
     return FHP_OK;
 }
@@ -1156,10 +1288,66 @@ int fhp_pool_admit(fhp_pool* pl, const fhp_params* p, uint64_t steps, uint32_t* 
     return FHP_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// A tick of `passes` passes as one tiled launch, where the pool takes tiles
+// (eng.tiles): passes * K steps of every job, and the rest of those left with
+// fewer than K.
+int pool_tick_tiles(fhp_pool* pl, uint32_t passes) {
+    Engine* e = &pl->eng;
+    const uint32_t K = e->depth, n = passes * K, tail = K - 1;
+    if (!pl->changed && !e->tiles) return FHP_OK;  // bands, chosen with these jobs
+    if (pl->changed || !e->tiles || e->tile_n < n + tail) {
+        std::vector<fhp_sim*> act;
+        std::vector<uint64_t> lim;
+        pl->table_slots.clear();
+        for (uint32_t i = 0; i < pl->slots.size(); i++) {
+            PoolSlot& s = pl->slots[i];
+            if (!s.used || s.remaining == 0) continue;
+            act.push_back(&s.sim);
+            lim.push_back(s.remaining);
+            pl->table_slots.push_back(i);
+        }
+        int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n + tail);
+        if (rc) return rc;
+        if (!e->tiles) {
+            pl->changed = 1;  // the band tables are to be built
+            return FHP_OK;
+        }
+        pl->changed = 0;
+    }
+    int rc = engine_tile_launch(e, n, tail);
+    if (rc) return rc;
+    for (uint32_t i : pl->table_slots) {  // host mirror of what the launch does
+        PoolSlot& s = pl->slots[i];
+        if (!s.used || s.remaining == 0) continue;
+        const uint64_t k = s.remaining <= n + tail ? s.remaining : n;
+        s.sim.t += k;
+        s.sim.cur ^= 1;
+        s.remaining -= k;
+        if (s.remaining == 0) pl->finished.push_back(i);
+    }
+    return FHP_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int fhp_pool_tick(fhp_pool* pl, uint32_t passes) {
     if (!pl) return fail(FHP_E_INVAL, "pool is NULL");
     if (!passes) passes = 1;
     const uint32_t K = pl->eng.depth;
+    if (!pl->own_band && passes <= (kTileMaxSteps + 1 - K) / K) {
+        int rc = pool_tick_tiles(pl, passes);
+        if (rc) return rc;
+        if (pl->eng.tiles) return FHP_OK;
+    } else if (pl->eng.tiles) {
+        pl->eng.tiles = false;
+        pl->changed = 1;
+    }
     // The tables list every job with full passes left and give each its total
     // count of full passes; the device counts them down, so the tables are
     // rebuilt only when jobs arrive or leave.

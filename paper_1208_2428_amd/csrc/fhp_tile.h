@@ -52,6 +52,21 @@ struct TileArgs {
     uint32_t chi_and, chi_or;
 };
 
+// One lattice of a tiled launch over many, and one tile of it.
+struct TileMember {
+    uint64_t* buf[2];
+    const uint64_t* S;
+    uint64_t ps, t0, key_chir, key_force;
+    uint32_t thr_force, chi_and, chi_or;
+    uint32_t H, wd, walls, cur;
+    uint32_t steps;  // steps it may still run (kNoStepLimit: no limit)
+    uint32_t T, C, out_words, tiles_x;
+};
+struct TileItem {
+    uint32_t m, tile;
+};
+constexpr uint32_t kNoStepLimit = 0xffffffffu;
+
 namespace {
 
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -68,15 +83,16 @@ struct TilePlace {
     uint32_t row_lo, row_hi;
 };
 
-__device__ __forceinline__ TilePlace tile_place(const TileArgs& a, bool valid, uint32_t row, uint32_t c,
-                                                uint32_t rows_each) {
+// tile: the tile's number in the lattice, row by row.
+__device__ __forceinline__ TilePlace tile_place(const TileArgs& a, uint32_t tile, bool valid, uint32_t row,
+                                                uint32_t c, uint32_t rows_each) {
     TilePlace p;
     p.valid = valid;
     p.c = c;
     p.row = row;
     p.full = a.tiles_x == 1;
-    p.ty = blockIdx.x / a.tiles_x;
-    p.tx = blockIdx.x - p.ty * a.tiles_x;
+    p.ty = tile / a.tiles_x;
+    p.tx = tile - p.ty * a.tiles_x;
     p.y = (p.ty * a.T + row + a.H - a.halo % a.H) % a.H;
     p.w = p.full ? c : (p.tx * a.out_words + c + a.wd - 1) % a.wd;
     p.cl = c ? c - 1 : (p.full ? a.C - 1 : 0);
@@ -201,7 +217,7 @@ __global__ void __launch_bounds__(NT) k_tile1(const uint64_t* __restrict__ in, u
     const uint32_t e = tid - (odd ? a.split : 0);
     const bool valid = e < half;
     const uint32_t er = valid ? e / a.C : 0, c = valid ? e - er * a.C : 0;
-    const TilePlace at = tile_place(a, valid, 2 * er + (odd ? 1u : 0u), c, 1);
+    const TilePlace at = tile_place(a, blockIdx.x, valid, 2 * er + (odd ? 1u : 0u), c, 1);
     const size_t idx = (size_t)at.y * a.wd + at.w;
     uint64_t p[7];
 #pragma unroll
@@ -235,19 +251,18 @@ constexpr int pair_waves() {
     return RULES == kRulesFHP3 ? 4 : 5;
 }
 
-// SOLID: the lattice has obstacles or walls.
+// One tile of a lattice from `in` to `out`.  SOLID: the lattice has obstacles
+// or walls.
 template <int NT, bool FORCE, bool SOLID, int RULES>
-__global__ void __launch_bounds__(NT, pair_waves<RULES>()) k_tile2(const uint64_t* __restrict__ in,
-                                                                uint64_t* __restrict__ out,
-                                                                const uint64_t* __restrict__ S,
-                                                                TileArgs a) {
-    __shared__ PairSlot<NT> slots[2];
+__device__ __forceinline__ void tile2(PairSlot<NT>* slots, const uint64_t* __restrict__ in,
+                                      uint64_t* __restrict__ out, const uint64_t* __restrict__ S,
+                                      const TileArgs& a, uint32_t tile) {
     const uint32_t rows = a.T + 2 * a.halo;
     const uint32_t tid = threadIdx.x;
     const bool valid = tid < rows / 2 * a.C;
     const uint32_t g = valid ? tid / a.C : 0, c = valid ? tid - g * a.C : 0;
     // H, T and halo are even: the pair never straddles the lattice's last row
-    const TilePlace at = tile_place(a, valid, 2 * g, c, 2);
+    const TilePlace at = tile_place(a, tile, valid, 2 * g, c, 2);
     const size_t idx = (size_t)at.y * a.wd + at.w;
     uint64_t pe[7], po[7];
 #pragma unroll
@@ -334,6 +349,50 @@ __global__ void __launch_bounds__(NT, pair_waves<RULES>()) k_tile2(const uint64_
     }
 }
 
+template <int NT, bool FORCE, bool SOLID, int RULES>
+__global__ void __launch_bounds__(NT, pair_waves<RULES>()) k_tile2(const uint64_t* __restrict__ in,
+                                                                   uint64_t* __restrict__ out,
+                                                                   const uint64_t* __restrict__ S,
+                                                                   TileArgs a) {
+    __shared__ PairSlot<NT> slots[2];
+    tile2<NT, FORCE, SOLID, RULES>(slots, in, out, S, a, blockIdx.x);
+}
+
+// Tiles of many lattices in one launch: workgroup b takes item b.  A lattice
+// takes part with `n` steps, or with the `left` ones it still has where they
+// are at most n + tail.  `done` steps and `launches` launches lie between the
+// tables and this launch.
+template <bool FORCE, bool SOLID, int RULES>
+__global__ void __launch_bounds__(kTileBatchThreads, pair_waves<RULES>())
+    k_tiles(const TileMember* __restrict__ members, const TileItem* __restrict__ items, uint32_t done,
+            uint32_t launches, uint32_t n, uint32_t tail) {
+    __shared__ PairSlot<kTileBatchThreads> slots[2];
+    const TileItem it = items[blockIdx.x];
+    const TileMember& M = members[it.m];
+    if (M.steps <= done) return;
+    const uint32_t left = M.steps - done;
+    TileArgs a;
+    a.H = M.H;
+    a.wd = M.wd;
+    a.C = M.C;
+    a.out_words = M.out_words;
+    a.tiles_x = M.tiles_x;
+    a.T = M.T;
+    a.steps = left <= n + tail ? left : n;
+    a.halo = (a.steps + 1) & ~1u;  // tile_halo
+    a.split = 0;
+    a.walls = M.walls;
+    a.ps = M.ps;
+    a.t0 = M.t0 + done;
+    a.key_chir = M.key_chir;
+    a.key_force = M.key_force;
+    a.thr_force = M.thr_force;
+    a.chi_and = M.chi_and;
+    a.chi_or = M.chi_or;
+    const uint32_t cur = (M.cur ^ launches) & 1;
+    tile2<kTileBatchThreads, FORCE, SOLID, RULES>(slots, M.buf[cur], M.buf[cur ^ 1], M.S, a, it.tile);
+}
+
 // Picks the kernel with the fewest LDS entries that hold nt threads.
 template <bool FORCE, int RULES>
 hipError_t launch_tile1(uint32_t grid, uint32_t nt, const uint64_t* in, uint64_t* out, const uint64_t* S,
@@ -373,5 +432,10 @@ hipError_t launch_tiles_1(uint32_t grid, uint32_t nt, bool force, uint32_t rules
                           uint64_t* out, const uint64_t* S, const TileArgs& a, hipStream_t st);
 hipError_t launch_tiles_2(uint32_t grid, uint32_t nt, bool force, uint32_t rules, const uint64_t* in,
                           uint64_t* out, const uint64_t* S, const TileArgs& a, hipStream_t st);
+// Tiles of many lattices (fhp_tile_batch.hip); solid: any lattice has
+// obstacles or walls.
+hipError_t launch_tile_items(uint32_t items_n, bool force, bool solid, uint32_t rules,
+                             const TileMember* members, const TileItem* items, uint32_t done,
+                             uint32_t launches, uint32_t n, uint32_t tail, hipStream_t st);
 
 }  // namespace fhp

@@ -24,6 +24,7 @@ namespace fhp {
 
 constexpr uint32_t kTileMaxSteps = 32;  // deepest tiled launch
 constexpr uint32_t kTileMaxThreads = 1024;
+constexpr uint32_t kTileBatchThreads = 512;  // workgroup of a launch over many lattices
 
 struct TilePlan {
     uint32_t R;  // rows per thread (0: no plan)
@@ -112,6 +113,37 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool
             for (uint32_t t : {256u, 384u, 512u, 640u, 768u, 1024u}) consider(1, C, t, n);
             for (uint32_t t : {320u, 512u, 640u, 768u, 1024u}) consider(2, C, t, n);
         }
+    }
+    return best;
+}
+
+// Shape of one lattice's tiles in a launch over many (two rows per thread,
+// workgroups of kTileBatchThreads): the fewest rows of 64 words updated per
+// step, tiles x live waves x 2 (`work`).
+struct TileShape {
+    uint32_t T, C;
+    uint32_t tiles;
+    double work;
+};
+
+inline TileShape tile_shape(uint32_t H, uint32_t wd, uint32_t n) {
+    TileShape best{0, 0, 0, 0.0};
+    const uint32_t halo = tile_halo(n);
+    const uint32_t widths[] = {5, 6, 8, 10, 13, 15, 18, 24, 34, 0};  // 0: full rows
+    for (uint32_t w : widths) {
+        if (w ? w >= wd : wd > 66) continue;
+        const uint32_t k = w ? (wd + w - 3) / (w - 2) : 1;
+        const uint32_t C = w ? (wd + k - 1) / k + 2 : wd;
+        if (w && C >= wd) continue;
+        const uint32_t fit = kTileBatchThreads / C;
+        if (2 * fit < 2 * halo + 2) continue;
+        uint32_t T = std::min(2 * fit - 2 * halo, H);
+        const uint32_t ty = (H + T - 1) / T;
+        T = ((H + ty - 1) / ty + 1) & ~1u;
+        const uint32_t rows = T + 2 * halo, tiles = ty * tiles_per_row(C, wd);
+        const double live = std::min(1.0, (double)(T + n + 1) / rows);
+        const double work = (double)tiles * (tile_threads(2, rows, C) / 64) * live * 2;
+        if (!best.T || work < best.work) best = {T, C, tiles, work};
     }
     return best;
 }
