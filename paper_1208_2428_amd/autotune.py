@@ -25,10 +25,11 @@ from ._binding import FhpError
 DEFAULT_BATCH_CANDIDATES = [
     dict(depth=k, band=b, group_threads=nt, passes_per_launch=ppl)
     for k in (1, 2, 3, 4, 5) for b in (8, 16, 32, 64) for nt in (64, 256) for ppl in (1, 0)
-]
+] + [dict(depth=0, band=0, group_threads=0, passes_per_launch=1)]  # the library's choice
 # 2- and 6-row bands: the best heights on lattices of 32- and 64-word rows
 # too small to give every SIMD two waves (2048^2, 4096^2)
-DEFAULT_SIM_CANDIDATES = [dict(depth=k, band=b) for k in (1, 2, 3, 4, 5) for b in (2, 4, 6, 8, 16, 32, 64)]
+DEFAULT_SIM_CANDIDATES = [dict(depth=k, band=b) for k in (1, 2, 3, 4, 5) for b in (2, 4, 6, 8, 16, 32, 64)] + \
+    [dict(depth=0, band=0)]  # the library's choice
 
 
 def cache_path() -> str:
@@ -125,7 +126,7 @@ def tune_batch(batch, params: list[dict], candidates=None, steps: int = 24,
     trials = []
     for cand in cands:
         batch.set_tiling(**cand)
-        per = cand["depth"] * 3
+        per = (cand["depth"] or 16) * 3
         n = max(per, (steps // per) * per)
         dt = time_steps(batch.step, batch.stream, n, 1)
         batch.sync()

@@ -174,11 +174,35 @@ uint32_t default_depth(uint32_t H, uint32_t wd, uint32_t simds) {
 }
 
 // Tiles against sweeping bands (default depth and band): lattices of up to
-// kTileNodes nodes run tiled passes.
+// kTileNodes nodes run tiled passes.  Measured us per step, tiles and sweep
+// (default bands; best bands): 8960 x 8192 8.0, 12.8; 12288 x 8192 10.0, 13.0;
+// 10.8; 12288^2 14.5, 17.5; 14.6; 16384 x 12288 18.8, 18.2; 17.6; 16384^2 25,
+// 22.  FHP-III the same way: 12288 x 8192 16.7, 20.8; 16384^2 49, 38.
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) {
-    constexpr uint64_t kTileNodes = 8192ull * 9216;
     if (n < 2 || (uint64_t)L.W * L.H > kTileNodes) return TilePlan{};
     return tile_plan(L.H, L.wd, simds / 4, D.rules == FHP_RULES_FHP3, D.thr_force != 0, n);
+}
+
+// Sweeping passes by default (lattices too large for tiles): depth 6 where
+// the default depth is FHP_MAX_DEPTH and one buffer resource spans the state
+// (FHP-III: 3), and the band height that takes the fewest row iterations,
+// rounds (T + 2 K), with two waves per SIMD at once.  Against bands of 32 rows
+// or the height that gives at least two waves per SIMD (default_band; us per
+// step): 16384 x 12288, 24 rows 18.2 -> 17.8; 15040 x 14002, 26 -> 28 rows
+// 27.4 -> 20; 10048 x 16384, 24 -> 32 rows 21.6 -> 18.0.
+void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint32_t* K, uint32_t* T) {
+    *K = depth;
+    if (D.rules == FHP_RULES_FHP3) *K = depth < kMaxDepthFHP3 ? depth : kMaxDepthFHP3;
+    else if (depth == FHP_MAX_DEPTH && 7 * L.ps * 8 <= 0xffffffffull) *K = kSweepDepth;
+    const uint32_t waves = (L.wd + 63) / 64, cus = simds / 4;
+    const uint64_t held = (uint64_t)cus * (waves < 8 ? 8 / waves : 1);  // bands at once
+    uint64_t best = ~0ull;
+    *T = 2;
+    for (uint32_t t = 8; t <= 128 && t <= L.H; t += 2) {
+        const uint64_t bands = (L.H + t - 1) / t;
+        const uint64_t cost = (bands + held - 1) / held * (t + 2 * *K);
+        if (cost < best) best = cost, *T = t;
+    }
 }
 
 Dyn dyn_for(const fhp_params* p) {
@@ -338,9 +362,13 @@ int fhp_step(fhp_sim* s, uint64_t n) {
     }
     uint32_t depth = s->depth;
     if (s->D.rules == FHP_RULES_FHP3 && depth > kMaxDepthFHP3) depth = kMaxDepthFHP3;
-    const uint32_t T = s->band ? s->band : default_band(s->L.H, s->L.wd, s->simds);
+    uint32_t T = s->band ? s->band : default_band(s->L.H, s->L.wd, s->simds);
+    const bool own = s->own_depth || s->band || L.wd > kMaxBlockedWords;
+    if (!own) plan_sweep(L, s->D, s->simds, s->depth, &depth, &T);
     while (n > 0) {
-        uint32_t k = (n >= depth) ? depth : (uint32_t)n;
+        // passes of `depth` steps and a shorter last one, or evenly deep
+        const uint64_t left = (n + depth - 1) / depth;
+        const uint32_t k = own ? (uint32_t)(n < depth ? n : depth) : (uint32_t)((n + left - 1) / left);
         if (fault_launch()) return hip_fail(hipErrorLaunchFailure, "step (injected by FHP_FAULT)");
         if (k == 1)
             FHP_HIP_TRY(launch_step1(s->buf[s->cur], s->buf[1 - s->cur], L, s->D, s->t, s->st),

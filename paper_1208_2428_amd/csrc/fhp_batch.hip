@@ -703,20 +703,30 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
 static_assert(sizeof(TileMember) <= sizeof(MemberDesc), "tile members use the member table's memory");
 static_assert(sizeof(TileItem) <= sizeof(GroupDesc), "tiles use the group and wave tables' memory");
 
-// Tiles against bands.  A sweep pass has two waves per SIMD only from about
-// kTileBatchWords words on; below, its launches wait for their level chains,
-// and tiles step faster whatever the members' sizes.
-constexpr uint64_t kTileBatchWords = 1600000;
+// Tiles against bands, by the deepest launch (n_max steps) and the members'
+// words.  Launches of 10 steps and more step any batch faster as tiles
+// (random sides up to 2048, us per step at 16 steps, tiles and bands: 60
+// lattices 10.4 and 20.5, 512 64 and 81; with forcing 11.8 and 21.0, 73 and
+// 109).  A launch of 5 to 9 steps recomputes and reloads more halo per step:
+// up to kTileBatchWords words, where a sweep has too few bands for two waves
+// per SIMD, tiles are faster (channels, 0.05 million words 1.8 and 19.5, 1.9
+// million 18.5 and 24.9), above it bands (3.5 million 32.8 and 27.9).
+constexpr uint64_t kTileBatchWords = 2500000;
+constexpr uint32_t kTileBatchDeep = 10;
 
-// Decides between tiles and bands for sims[0..n) and calls of `steps` steps
-// (n_max: most steps per launch) and, for tiles, builds and uploads the tables.
-// limit: steps each may still run, or nullptr.  Leaves e->tiles.
-int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_t n, uint32_t n_max) {
+// Decides between tiles and bands for sims[0..n) and launches of `n_min` to
+// `n_max` steps and, for tiles, builds and uploads the tables.  limit: steps
+// each may still run, or nullptr.  Leaves e->tiles.
+int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_t n, uint32_t n_min,
+                 uint32_t n_max) {
     e->tiles = false;
     if (n == 0 || n > e->max_members) return FHP_OK;
     uint64_t words = 0;
-    for (uint32_t i = 0; i < n; i++) words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
-    if (words > kTileBatchWords) return FHP_OK;
+    for (uint32_t i = 0; i < n; i++) {
+        words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
+        if ((uint64_t)sims[i]->L.W * sims[i]->L.H > kTileNodes) return FHP_OK;
+    }
+    if (words > kTileBatchWords && n_min < kTileBatchDeep) return FHP_OK;
     std::vector<TileShape> shapes(n);
     uint64_t items = 0;
     for (uint32_t i = 0; i < n; i++) {
@@ -938,6 +948,7 @@ struct fhp_batch {
     Engine eng;
     bool tables_dirty;  // tiling changed: rebuild before the next step
     bool own_tiling;    // the caller chose the tiling: sweeping bands
+    bool shallow;       // the last call's launches were too shallow for its words as tiles
     int changed;        // set by member handles when a member is changed alone
 };
 
@@ -1017,11 +1028,18 @@ constexpr uint32_t kBatchTileSteps = 16;
 int batch_step_tiles(fhp_batch* b, uint64_t n) {
     Engine* e = &b->eng;
     const uint64_t launches = (n + kBatchTileSteps - 1) / kBatchTileSteps;
-    const uint32_t deepest = (uint32_t)((n + launches - 1) / launches);
+    const uint32_t shallowest = (uint32_t)(n / launches), deepest = (uint32_t)((n + launches - 1) / launches);
+    // A second call in a row that bands step faster goes back to them; a
+    // single one does not change tables.
+    uint64_t words = 0;
+    for (uint32_t i = 0; i < b->n; i++) words += (uint64_t)b->sims[i].L.H * b->sims[i].L.wd;
+    const bool shallow = words > kTileBatchWords && shallowest < kTileBatchDeep;
+    if (e->tiles && shallow && b->shallow) e->tiles = false;
+    b->shallow = shallow;
     // the tables hold while nobody else steps the members and their step
     // counter has room
     if (!e->tiles || b->changed || e->tile_n < deepest || e->tile_done + n >= kTimeLimit) {
-        int rc = engine_tiles(e, b->ptrs.data(), nullptr, b->n, deepest);
+        int rc = engine_tiles(e, b->ptrs.data(), nullptr, b->n, shallowest, deepest);
         if (rc) return rc;
         b->tables_dirty = true;  // the band tables are gone
         b->changed = 0;
@@ -1310,7 +1328,7 @@ int pool_tick_tiles(fhp_pool* pl, uint32_t passes) {
             lim.push_back(s.remaining);
             pl->table_slots.push_back(i);
         }
-        int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n + tail);
+        int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n, n + tail);
         if (rc) return rc;
         if (!e->tiles) {
             pl->changed = 1;  // the band tables are to be built

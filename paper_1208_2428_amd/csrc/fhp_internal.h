@@ -32,6 +32,12 @@ struct Dyn {
 // of an FHP-III lattice are at most three steps deep.
 constexpr uint32_t kMaxDepthFHP3 = 3;
 
+// Largest lattice that runs tiled passes by default (plan_tiles).
+constexpr uint64_t kTileNodes = 12288ull * 12288;
+
+// Depth of the sweeping passes that large lattices run by default.
+constexpr uint32_t kSweepDepth = 6;
+
 // Workspace layout of one lattice: [buffer 0: 7 planes][buffer 1: 7 planes]
 // [S plane][aux].
 struct Layout {
@@ -99,6 +105,9 @@ hipError_t launch_stepk(uint32_t K, const uint64_t* in, uint64_t* out, const Lat
 // `steps` (at most P.n) steps in one tiled pass (fhp_tile1.hip).
 hipError_t launch_tile(const TilePlan& P, uint32_t steps, const uint64_t* in, uint64_t* out,
                        const Lattice& L, const Dyn& D, uint64_t t, hipStream_t st);
+// Depth and band height of the sweeping passes of a lattice of default depth
+// `depth`, where the caller chose neither.
+void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint32_t* K, uint32_t* T);
 // The tiled passes for n steps of a lattice, or no plan (R = 0) where
 // sweeping bands are faster.
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n);

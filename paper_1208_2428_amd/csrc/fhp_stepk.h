@@ -1,5 +1,5 @@
 // fhp_stepk.h -- temporally blocked FHP update: K time steps per pass over
-// HBM (K = 1..FHP_MAX_DEPTH).
+// HBM (K = 1..FHP_MAX_DEPTH, and 6 by default on large lattices).
 //
 // Decomposition.  A workgroup owns a band of T consecutive rows (T even) and
 // the full lattice width: thread w holds 64-node word w of every row it
@@ -359,6 +359,9 @@ hipError_t launch_stepk_wide(uint32_t K, const uint64_t* in, uint64_t* out, cons
 // The depth-5 pass with LDS carries and the streamed fill, for state buffers
 // below 4 GiB (fhp_stepk_k5.hip, compiled with its own instruction schedule).
 hipError_t launch_stepk_k5(const uint64_t* in, uint64_t* out, const Lattice& L, const StepkArgs& a,
+                           uint32_t rules, hipStream_t st);
+// The depth-6 pass, the same way (FHP-I and FHP-II).
+hipError_t launch_stepk_k6(const uint64_t* in, uint64_t* out, const Lattice& L, const StepkArgs& a,
                            uint32_t rules, hipStream_t st);
 // The pass for rows of a power of two words up to 64, one wave per band
 // (fhp_stepk_wave.hip).

@@ -26,6 +26,7 @@ hipError_t launch_stepk(uint32_t K, const uint64_t* in, uint64_t* out, const Lat
     // bands of a 4096 x 65536 lattice -25%, 16384^2 at 16 and 32 rows -10% and
     // -8%), and rows of 128 words gain nothing at 4 or 8 rows.
     a.xcd_runs = (L.wd <= 64 && a.T <= 8) ? 1u : 0u;
+    if (K == kSweepDepth) return launch_stepk_k6(in, out, L, a, D.rules, st);
     if (planes_wide(L.ps)) return launch_stepk_wide(K, in, out, L, a, D.rules, st);
     // At most one wave per SIMD: nothing hides a wave's load latency, and the
     // preloaded pipeline fill pays: on 4096^2 +8% at K = 3 and +11% at K = 5

@@ -411,12 +411,8 @@ hipError_t launch_tile1(uint32_t grid, uint32_t nt, const uint64_t* in, uint64_t
 template <bool FORCE, bool SOLID, int RULES>
 hipError_t launch_tile2(uint32_t grid, uint32_t nt, const uint64_t* in, uint64_t* out, const uint64_t* S,
                         const TileArgs& a, hipStream_t st) {
-    if (nt <= 320)
-        hipLaunchKernelGGL((k_tile2<320, FORCE, SOLID, RULES>), dim3(grid), dim3(nt), 0, st, in, out, S, a);
-    else if (nt <= 512)
+    if (nt <= 512)
         hipLaunchKernelGGL((k_tile2<512, FORCE, SOLID, RULES>), dim3(grid), dim3(nt), 0, st, in, out, S, a);
-    else if (nt <= 640)
-        hipLaunchKernelGGL((k_tile2<640, FORCE, SOLID, RULES>), dim3(grid), dim3(nt), 0, st, in, out, S, a);
     else if (nt <= 1024)
         hipLaunchKernelGGL((k_tile2<1024, FORCE, SOLID, RULES>), dim3(grid), dim3(nt), 0, st, in, out, S, a);
     else

@@ -5,15 +5,7 @@
 // times and stores its T x out_words own words.  Deeper launches spread the
 // launch, the loads and the stores over more steps but recompute more halo;
 // larger tiles recompute less of it but leave fewer workgroups.  The choice is
-// the cheapest shape under a model of a launch's time,
-//   A + rounds B + n (rounds L + work c)  microseconds,
-// rounds = workgroups a compute unit runs one after the other, work = rows of
-// 64 words a SIMD updates per step.  Its constants are fitted to 900 measured
-// launches of 20 lattices from 64^2 to 16384^2 (model over measured 0.85 to
-// 1.15 for 80% of them).  Over those lattices the shape it picks is within 10%
-// of the fastest one measured, 1% in the median: 256^2 0.54 us per step (the
-// fastest 0.53), 1024^2 0.75 (0.74), 2048^2 1.04 (1.04), 4096^2 2.20 (2.11),
-// 8192 x 8128 8.3 (7.5).
+// the cheapest shape under a model of a launch's time (tile_plan).
 #pragma once
 
 #include <stdint.h>
@@ -49,17 +41,23 @@ inline uint32_t tiles_per_row(uint32_t C, uint32_t wd) {
     return (wd + o - 1) / o;
 }
 
-// Model constants by rows per thread: FHP-I and FHP-II with forcing, FHP-III.
-struct TileModel {
-    double A, B, L, c;
-};
-constexpr TileModel kTileModel[2][2] = {{{0.0, 7.7, 0.0, 0.33}, {1.9, 8.2, 0.0, 0.266}},
-                                        {{4.8, 4.1, 0.07, 0.55}, {0.4, 9.5, 0.62, 0.40}}};
-
 // The cheapest shape for `steps` steps of an H x wd-word lattice on `cus`
-// compute units.  Without forcing a step has 0.8 times the arithmetic.
+// compute units.  A step costs a SIMD `work` rows of 64 words: its waves (a
+// workgroup's count rounded up to four, one per SIMD: 7 waves cost more than
+// 8) times the rows each holds, less those that no longer matter.
+//  - Workgroups that have their compute unit to themselves (all tiles in one
+//    round, or 1024 threads of two rows): 5 us + 0.36 us a row with one row
+//    per thread, 6.5 + 0.30 with two.
+//  - Two workgroups per compute unit, one working while the other waits at its
+//    barrier: 4 us, and per round 3 us + 0.255 or 0.24 us a row (0.27 or 0.29
+//    where a single round starts them all together).
+// Fitted to launches of 20 lattices from 64^2 to 16384^2 (FHP-II with forcing;
+// FHP-III takes 1.7 times the arithmetic, no forcing 0.87).  Measured us per
+// step of the shape it picks, and of the fastest one found: 256^2 0.53, 0.53;
+// 1024^2 0.75, 0.74; 2048^2 1.02, 1.02; 4096^2 2.1, 2.1; 8192 x 8128 7.3, 7.2.
 inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool force, uint64_t steps) {
     TilePlan best{};
+    const double alu = (fhp3 ? 1.7 : 1.0) * (force ? 1.0 : 0.87);
     auto consider = [&](uint32_t R, uint32_t C, uint32_t threads, uint32_t n) {
         const uint32_t halo = tile_halo(n);
         // the most rows whose threads fit (an even number of waves for R = 1)
@@ -70,21 +68,24 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool
         T = ((H + ty - 1) / ty + 1) & ~1u;  // the same number of tiles, even ones
         const uint32_t rows = T + 2 * halo, waves = tile_threads(R, rows, C) / 64;
         const uint64_t grid = (uint64_t)ty * tiles_per_row(C, wd);
-        // workgroups a compute unit holds: by registers 24 waves (R = 2 and
-        // FHP-III: 20 and 16), by its 160 KB of LDS 80 bytes (R = 2: 112) per
-        // thread of the kernel's size
-        const uint32_t lds = R == 1 ? (threads <= 256 ? 8 : threads <= 512 ? 4 : 2)
-                                    : (threads <= 320 ? 4 : threads <= 640 ? 2 : 1);
-        const uint32_t regs = (fhp3 ? 16u : R == 1 ? 24u : 20u) / waves;
-        const uint32_t held = std::max(1u, std::min(lds, regs));
         const uint64_t per_cu = (grid + cus - 1) / cus;
-        const double rounds = (double)((per_cu + held - 1) / held);
         // rows beyond those that still matter are skipped wave by wave
         const double live = std::min(1.0, (double)(T + n - 1 + R) / rows);
-        const double work = std::max(live * ((per_cu * waves + 3) / 4), 1.0) * R;
-        const TileModel& m = kTileModel[fhp3][R - 1];
-        const double launch = m.A + m.B * rounds;
-        const double step = m.L * rounds + work * m.c * (force ? 1.0 : 0.8);
+        const double row = live * ((waves + 3) / 4) * R;  // of one workgroup, on each SIMD
+        // LDS: 160 KB hold two workgroups, but one of 1024 threads with R = 2
+        // (and registers one of more than 768 with R = 1)
+        const bool two = R == 1 ? threads <= (fhp3 ? 640u : 768u) : threads <= 512;
+        double launch, step;
+        if (per_cu == 1 || !two) {
+            launch = (R == 1 ? 5.0 : 6.5) * per_cu;
+            step = per_cu * std::max(row, (double)R) * (R == 1 ? 0.36 : 0.30) * alu;
+        } else {
+            const double x = (double)grid / (2.0 * cus);
+            const double rounds = x <= 1.0 ? 1.0 : x + 0.3;
+            launch = 4.0 + 3.0 * rounds;
+            const double c = x <= 1.0 ? (R == 1 ? 0.27 : 0.29) : (R == 1 ? 0.255 : 0.24);
+            step = rounds * 2 * row * c * alu;
+        }
         const uint64_t launches = (steps + n - 1) / n;
         const double us = launches * launch + (double)steps * step;
         if (best.R == 0 || us < best.us) {
@@ -95,7 +96,7 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool
             best.us = us;
         }
     };
-    const uint32_t depths[] = {8, 12, 16, 20, 24, 28, kTileMaxSteps};
+    const uint32_t depths[] = {8, 10, 12, 16, 20, 24, 28, kTileMaxSteps};
     const uint32_t widths[] = {5, 6, 8, 10, 13, 15, 18, 24, 34, 0};  // 0: full rows
     uint32_t last_n = 0;
     for (uint32_t n : depths) {
@@ -110,8 +111,8 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool
             const uint32_t C = w ? (wd + k - 1) / k + 2 : wd;
             if (C == last_C || (w && C >= wd)) continue;
             last_C = C;
-            for (uint32_t t : {256u, 384u, 512u, 640u, 768u, 1024u}) consider(1, C, t, n);
-            for (uint32_t t : {320u, 512u, 640u, 768u, 1024u}) consider(2, C, t, n);
+            for (uint32_t t : {256u, 512u, 768u, 1024u}) consider(1, C, t, n);
+            for (uint32_t t : {512u, 1024u}) consider(2, C, t, n);
         }
     }
     return best;
