@@ -22,30 +22,26 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Bytes of the idle buffer, used as staging for host transfers.
 size_t staging_bytes(const fhp_sim* s) { return s->lay.buf_words * sizeof(uint64_t); }
 
-int refresh_has_mask(fhp_sim* s) {
-    FHP_HIP_TRY(launch_fill_u64(s->aux, 1, 0, s->st), "clear aux");
-    FHP_HIP_TRY(launch_or_reduce(s->S, (size_t)s->L.H * s->L.wd, s->aux, s->st), "mask reduce");
-    uint64_t any = 0;
-    FHP_HIP_TRY(hipMemcpyAsync(&any, s->aux, sizeof(any), hipMemcpyDeviceToHost, s->st), "copy");
-    FHP_HIP_TRY(hipStreamSynchronize(s->st), "sync");
-    s->has_mask = any != 0;
-    return FHP_OK;
-}
-
-// Uploads W*H bytes in row chunks through the idle buffer and packs them.
+// Uploads W*H bytes in row chunks through the idle buffer and packs them;
+// has_mask = an obstacle is among them.
 int upload_bytes(fhp_sim* s, const uint8_t* host, int mask_only) {
     const uint32_t W = s->L.W, H = s->L.H;
     uint8_t* stage = (uint8_t*)s->buf[1 - s->cur];
     uint32_t rows = (uint32_t)(staging_bytes(s) / W);
     if (rows > H) rows = H;
+    FHP_HIP_TRY(launch_fill_u64(s->aux, 1, 0, s->st), "clear aux");
     for (uint32_t r0 = 0; r0 < H; r0 += rows) {
         const uint32_t n = (r0 + rows <= H) ? rows : H - r0;
         FHP_HIP_TRY(hipMemcpyAsync(stage, host + (size_t)r0 * W, (size_t)n * W,
                                    hipMemcpyHostToDevice, s->st), "upload");
-        FHP_HIP_TRY(launch_pack(stage, r0, n, s->L, s->buf[s->cur], s->S, mask_only, s->st),
+        FHP_HIP_TRY(launch_pack(stage, r0, n, s->L, s->buf[s->cur], s->S, mask_only, s->aux, s->st),
                     "pack");
         FHP_HIP_TRY(hipStreamSynchronize(s->st), "sync");  // the stage is reused
     }
+    uint64_t any = 0;
+    FHP_HIP_TRY(hipMemcpyAsync(&any, s->aux, sizeof(any), hipMemcpyDeviceToHost, s->st), "copy");
+    FHP_HIP_TRY(hipStreamSynchronize(s->st), "sync");
+    s->has_mask = any != 0;
     return FHP_OK;
 }
 }  // namespace
@@ -260,8 +256,6 @@ int sim_setup(fhp_sim* s, const fhp_params* p, uint64_t* planes, const Layout& l
     if (p->solid) {
         int r = upload_bytes(s, p->solid, 1);
         if (r) return r;
-        r = refresh_has_mask(s);
-        if (r) return r;
     }
     const uint64_t thr_fill = (uint64_t)floor(p->fill * 4294967296.0);  // fill * 2^32
     FHP_HIP_TRY(launch_init(s->buf[0], lattice_of(s), hash64(p->seed, kTagInit), thr_fill, st),
@@ -472,8 +466,6 @@ int fhp_set_state(fhp_sim* s, const uint8_t* host_src, size_t bytes, uint64_t t)
     if (t >= kTimeLimit) return fail(FHP_E_STATE, "time %llu at or above 2^24", (unsigned long long)t);
     if (s->changed) *s->changed = 1;
     int rc = upload_bytes(s, host_src, 0);
-    if (rc) return rc;
-    rc = refresh_has_mask(s);
     if (rc) return rc;
     s->t = t;
     return FHP_OK;

@@ -81,13 +81,14 @@ uint32_t device_simds();
 // Kernel launchers (fhp_kernels.hip).  All enqueue on `st` and return the HIP
 // launch status.
 hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t st);
+// Packs `rows` rows of bytes (16-byte aligned) from row row0 on; sets *any
+// when an obstacle is among them.
 hipError_t launch_pack(const uint8_t* bytes, uint32_t row0, uint32_t rows, const Lattice& L,
-                       uint64_t* planes, uint64_t* S, int mask_only, hipStream_t st);
+                       uint64_t* planes, uint64_t* S, int mask_only, uint64_t* any, hipStream_t st);
 hipError_t launch_unpack(const uint64_t* planes, const Lattice& L, uint32_t row0, uint32_t rows,
                          uint8_t* bytes, hipStream_t st);
 hipError_t launch_init(uint64_t* planes, const Lattice& L, uint64_t key_init, uint64_t thr_fill,
                        hipStream_t st);
-hipError_t launch_or_reduce(const uint64_t* p, size_t n, uint64_t* acc, hipStream_t st);
 hipError_t launch_observe_global(const uint64_t* planes, const Lattice& L, uint64_t* acc,
                                  hipStream_t st);
 hipError_t launch_observe_rows(const uint64_t* planes, const Lattice& L, uint32_t row0,

@@ -25,110 +25,148 @@ __global__ void __launch_bounds__(kBlock) k_fill_u64(uint64_t* p, size_t n, uint
     if (i < n) p[i] = v;
 }
 
-// bytes -> bit-planes.  One wave per 64-node word: lane b reads node 64w+b and
-// a wave ballot gathers bit c of the 64 nodes into plane c's word.
-// mask_only: every nonzero byte is an obstacle (S only).  Otherwise bits 0-6
-// go to the 7 planes and bit 7 to S.
-__global__ void __launch_bounds__(kBlock) k_pack(const uint8_t* __restrict__ bytes, uint32_t row0,
-                                                 uint32_t rows, Lattice L,
-                                                 uint64_t* __restrict__ planes,
-                                                 uint64_t* __restrict__ S, int mask_only) {
-    const uint32_t lane = threadIdx.x & 63;
-    const size_t word = ((size_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    if (word >= (size_t)rows * L.wd) return;  // whole wave exits together
-    const uint32_t ry = (uint32_t)(word / L.wd), w = (uint32_t)(word % L.wd);
-    const uint8_t v = bytes[(size_t)ry * L.W + 64u * w + lane];
-    const size_t idx = (size_t)(row0 + ry) * L.wd + w;
-    if (mask_only) {
-        const uint64_t m = __ballot(v != 0);
-        if (lane == 0) S[idx] = m;
-        return;
-    }
-    uint64_t words[8];
-#pragma unroll
-    for (int c = 0; c < 8; c++) words[c] = __ballot((v >> c) & 1);
-    if (lane < 7) planes[(size_t)lane * L.ps + idx] = words[lane];
-    if (lane == 7) S[idx] = words[7];
+// Bit k of the byte j of x, for the four bytes, as the low four bits.
+__device__ __forceinline__ uint32_t gather4(uint32_t x, uint32_t k) {
+    return (((x >> k) & 0x01010101u) * 0x10204080u) >> 28;
+}
+// The inverse: bits 0..3 of x (the others ignored) as the low bits of four bytes.
+__device__ __forceinline__ uint32_t spread4(uint32_t x) {
+    return ((x & 0xfu) * 0x00204081u) & 0x01010101u;
 }
 
-// bit-planes -> bytes (bit 7 = obstacle or wall row).
+// Sets *any when v is nonzero in some lane, with an atomic only where it is
+// not set already (one per wave on a mask of many words had taken longer than
+// reading it: 48 us for a 2 MB plane).
+__device__ __forceinline__ void note_any(bool v, unsigned long long* any) {
+    if (__ballot(v) && (threadIdx.x & 63) == 0 &&
+        __hip_atomic_load(any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+        atomicOr(any, 1ull);
+}
+
+// bytes -> bit-planes, 16 nodes per thread: a 16-byte load, and a 16-bit store
+// per plane, so that a wave reads and writes whole lines (one node per thread
+// and a ballot per plane took 40 us for 4032 x 4090 nodes, this 9).
+// mask_only: every nonzero byte is an obstacle (S only).  Otherwise bits 0-6
+// go to the 7 planes and bit 7 to S.  *any is set when S has an obstacle.
+__global__ void __launch_bounds__(kBlock) k_pack(const uint4* __restrict__ bytes, uint32_t row0,
+                                                 uint32_t rows, Lattice L,
+                                                 uint64_t* __restrict__ planes,
+                                                 uint64_t* __restrict__ S, int mask_only,
+                                                 unsigned long long* any) {
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;  // 16-node piece of the rows
+    uint32_t solid = 0;
+    if (i < (size_t)rows * L.wd * 4) {
+        const uint4 q = bytes[i];
+        const uint32_t x[4] = {q.x, q.y, q.z, q.w};
+        const size_t o = (size_t)row0 * L.wd * 4 + i;
+        if (mask_only) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                // bit 7 of every nonzero byte
+                const uint32_t nz = ((x[j] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x[j];
+                solid |= gather4(nz, 7) << (4 * j);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 7; c++) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int j = 0; j < 4; j++) v |= gather4(x[j], c) << (4 * j);
+                ((uint16_t*)(planes + c * L.ps))[o] = (uint16_t)v;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) solid |= gather4(x[j], 7) << (4 * j);
+        }
+        ((uint16_t*)S)[o] = (uint16_t)solid;
+    }
+    note_any(solid != 0, any);
+}
+
+// bit-planes -> bytes (bit 7 = obstacle or wall row), 16 nodes per thread.
+// (A byte per thread took 58 us for 4032 x 4090 nodes, this 14.)
 __global__ void __launch_bounds__(kBlock) k_unpack(const uint64_t* __restrict__ planes, Lattice L,
                                                    uint32_t row0, uint32_t rows,
-                                                   uint8_t* __restrict__ bytes) {
-    const uint32_t lane = threadIdx.x & 63;
-    const size_t word = ((size_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    if (word >= (size_t)rows * L.wd) return;
-    const uint32_t ry = (uint32_t)(word / L.wd), w = (uint32_t)(word % L.wd);
-    const uint32_t y = row0 + ry;
-    const size_t idx = (size_t)y * L.wd + w;
-    uint32_t v = 0;
+                                                   uint4* __restrict__ bytes) {
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= (size_t)rows * L.wd * 4) return;
+    const size_t o = (size_t)row0 * L.wd * 4 + i;
+    const uint32_t y = row0 + (uint32_t)(i / (L.wd * 4));
+    uint32_t solid = L.S ? ((const uint16_t*)L.S)[o] : 0u;
+    if (L.walls && (y == 0 || y == L.H - 1)) solid = 0xffffu;
+    uint32_t v[4];
 #pragma unroll
-    for (int c = 0; c < 7; c++) v |= (uint32_t)((planes[(size_t)c * L.ps + idx] >> lane) & 1) << c;
-    v |= (uint32_t)((solid_word(L, y, idx) >> lane) & 1) << 7;
-    bytes[(size_t)ry * L.W + 64u * w + lane] = (uint8_t)v;
+    for (int j = 0; j < 4; j++) v[j] = spread4(solid >> (4 * j)) << 7;
+#pragma unroll
+    for (int c = 0; c < 7; c++) {
+        const uint32_t x = ((const uint16_t*)(planes + c * L.ps))[o];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] |= spread4(x >> (4 * j)) << c;
+    }
+    bytes[i] = make_uint4(v[0], v[1], v[2], v[3]);
 }
 
 // Initial state: fluid node bit c set iff
 // (H(key_init, c*2^40 + y*2^20 + x) >> 32) < thr_fill; solid nodes empty.
+// One wave per word, a lane per node, a ballot per plane: 7 hashes in a row
+// where a thread per word had 448, which kept a small lattice's few waves
+// busy for 28 us.
 __global__ void __launch_bounds__(kBlock) k_init(uint64_t* __restrict__ planes, Lattice L,
                                                  uint64_t key_init, uint64_t thr_fill) {
-    const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= (size_t)L.H * L.wd) return;
-    const uint32_t y = (uint32_t)(idx / L.wd), w = (uint32_t)(idx % L.wd);
-    const uint64_t fluid = ~solid_word(L, y, idx);
-    for (uint64_t c = 0; c < 7; c++) {
+    const uint32_t lane = threadIdx.x & 63;
+    const size_t n = (size_t)L.H * L.wd, stride = (size_t)gridDim.x * (kBlock / 64);
+    const uint32_t thr = (uint32_t)thr_fill;
+    const uint64_t full = thr_fill >> 32 ? ~0ull : 0ull;  // fill = 1
+    for (size_t idx = (size_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+         idx < n; idx += stride) {
+        const uint32_t y = (uint32_t)(idx / L.wd), w = (uint32_t)(idx - (size_t)y * L.wd);
+        const uint64_t fluid = ~solid_word(L, y, idx);
+        const uint64_t z0 = key_init + (((uint64_t)y << 20) + 64ull * w + lane + 1) * kGamma;
         uint64_t word = 0;
-        const uint64_t base = (c << 40) + ((uint64_t)y << 20) + 64ull * w;
-        for (uint32_t b = 0; b < 64; b++) {
-            const uint64_t h = hash64(key_init, base + b);
-            word |= (uint64_t)((h >> 32) < thr_fill) << b;
+#pragma unroll
+        for (uint64_t c = 0; c < 7; c++) {
+            const uint64_t h = mix64(z0 + (c << 40) * kGamma);
+            const uint64_t bits = __ballot((uint32_t)(h >> 32) < thr) | full;
+            word = lane == c ? bits : word;
         }
-        planes[c * L.ps + idx] = word & fluid;
+        if (lane < 7) planes[lane * L.ps + idx] = word & fluid;
     }
-}
-
-__global__ void __launch_bounds__(kBlock) k_or_reduce(const uint64_t* __restrict__ p, size_t n,
-                                                      unsigned long long* acc) {
-    size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    uint64_t v = 0;
-    for (; i < n; i += (size_t)gridDim.x * kBlock) v |= p[i];
-    // wave-level OR, then one atomic per wave
-    for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0 && v) atomicOr(acc, (unsigned long long)v);
 }
 
 // Momentum of channel c in units (1/2, sqrt(3)/2); c_i at (i-2)*60 degrees.
 __constant__ int kPx[7] = {-1, 1, 2, 1, -1, -2, 0};
 __constant__ int kPy[7] = {-1, -1, 0, 1, 1, 0, 0};
 
-// acc[0..10] += mass, p_x, p_y, count of channels 0..6, solid nodes.
+// acc[0..10] += mass, p_x, p_y, count of channels 0..6, solid nodes.  A thread
+// counts channels and solid nodes; the sums follow from the workgroup's counts.
 __global__ void __launch_bounds__(kBlock) k_observe_global(const uint64_t* __restrict__ planes,
                                                            Lattice L, unsigned long long* acc) {
-    __shared__ long long part[kBlock / 64][11];
-    long long v[11] = {0};
+    __shared__ uint32_t part[kBlock / 64][8];
+    uint32_t v[8] = {0};
     const size_t n = (size_t)L.H * L.wd;
     for (size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x; idx < n;
          idx += (size_t)gridDim.x * kBlock) {
         const uint32_t y = (uint32_t)(idx / L.wd);
-        for (int c = 0; c < 7; c++) {
-            const long long k = __popcll(planes[(size_t)c * L.ps + idx]);
-            v[0] += k;
-            v[1] += kPx[c] * k;
-            v[2] += kPy[c] * k;
-            v[3 + c] += k;
-        }
-        v[10] += __popcll(solid_word(L, y, idx));
+#pragma unroll
+        for (int c = 0; c < 7; c++) v[c] += __popcll(planes[(size_t)c * L.ps + idx]);
+        v[7] += __popcll(solid_word(L, y, idx));
     }
-    for (int j = 0; j < 11; j++)
+#pragma unroll
+    for (int j = 0; j < 8; j++)
         for (int off = 32; off > 0; off >>= 1) v[j] += __shfl_xor(v[j], off);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
-        for (int j = 0; j < 11; j++) part[wave][j] = v[j];
+        for (int j = 0; j < 8; j++) part[wave][j] = v[j];
     __syncthreads();
     if (threadIdx.x < 11) {
-        long long s = 0;
-        for (int k = 0; k < kBlock / 64; k++) s += part[k][threadIdx.x];
-        atomicAdd(acc + threadIdx.x, (unsigned long long)s);
+        const int t = threadIdx.x;
+        long long sum = 0;
+        for (int c = 0; c < 8; c++) {
+            long long k = 0;
+            for (int q = 0; q < kBlock / 64; q++) k += part[q][c];
+            const int f = t == 10 ? (c == 7) : c == 7 ? 0 : t == 0 ? 1 : t == 1 ? kPx[c] : t == 2 ? kPy[c] : (c == t - 3);
+            sum += f * k;
+        }
+        atomicAdd(acc + t, (unsigned long long)sum);
     }
 }
 
@@ -215,7 +253,13 @@ __global__ void __launch_bounds__(kBlock) k_digest(const uint64_t* __restrict__ 
         d += hash64(solid_word(L, y, idx), counter(7, y, w));
     }
     for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
-    if ((threadIdx.x & 63) == 0) atomicAdd(acc, (unsigned long long)d);
+    __shared__ uint64_t part[kBlock / 64];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kBlock / 64; q++) d += part[q];
+        atomicAdd(acc, (unsigned long long)d);
+    }
 }
 
 // One time step t -> t+1, one thread per 64-node word (y, w).
@@ -267,9 +311,12 @@ __global__ void __launch_bounds__(kBlock) k_step1(const uint64_t* __restrict__ i
 }
 
 unsigned grid_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+// Workgroups of a kernel that ends in atomics on one line: a few per compute
+// unit (4032 of them on a 4032 x 4090 lattice had cost the digest 40 of its
+// 53 us).
 unsigned grid_capped(size_t n) {
     const size_t g = (n + kBlock - 1) / kBlock;
-    return (unsigned)(g < 4096 ? (g ? g : 1) : 4096);
+    return (unsigned)(g < 512 ? (g ? g : 1) : 512);
 }
 
 }  // namespace
@@ -281,33 +328,28 @@ hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t st) {
 }
 
 hipError_t launch_pack(const uint8_t* bytes, uint32_t row0, uint32_t rows, const Lattice& L,
-                       uint64_t* planes, uint64_t* S, int mask_only, hipStream_t st) {
-    const size_t threads = (size_t)rows * L.wd * 64;
+                       uint64_t* planes, uint64_t* S, int mask_only, uint64_t* any, hipStream_t st) {
+    const size_t threads = (size_t)rows * L.wd * 4;
     if (!threads) return hipSuccess;
-    hipLaunchKernelGGL(k_pack, dim3(grid_for(threads)), dim3(kBlock), 0, st, bytes, row0, rows, L,
-                       planes, S, mask_only);
+    hipLaunchKernelGGL(k_pack, dim3(grid_for(threads)), dim3(kBlock), 0, st, (const uint4*)bytes, row0,
+                       rows, L, planes, S, mask_only, (unsigned long long*)any);
     return hipGetLastError();
 }
 
 hipError_t launch_unpack(const uint64_t* planes, const Lattice& L, uint32_t row0, uint32_t rows,
                          uint8_t* bytes, hipStream_t st) {
-    const size_t threads = (size_t)rows * L.wd * 64;
+    const size_t threads = (size_t)rows * L.wd * 4;
     if (!threads) return hipSuccess;
     hipLaunchKernelGGL(k_unpack, dim3(grid_for(threads)), dim3(kBlock), 0, st, planes, L, row0,
-                       rows, bytes);
+                       rows, (uint4*)bytes);
     return hipGetLastError();
 }
 
 hipError_t launch_init(uint64_t* planes, const Lattice& L, uint64_t key_init, uint64_t thr_fill,
                        hipStream_t st) {
-    hipLaunchKernelGGL(k_init, dim3(grid_for((size_t)L.H * L.wd)), dim3(kBlock), 0, st, planes, L,
-                       key_init, thr_fill);
-    return hipGetLastError();
-}
-
-hipError_t launch_or_reduce(const uint64_t* p, size_t n, uint64_t* acc, hipStream_t st) {
-    hipLaunchKernelGGL(k_or_reduce, dim3(grid_capped(n)), dim3(kBlock), 0, st, p, n,
-                       (unsigned long long*)acc);
+    const size_t blocks = ((size_t)L.H * L.wd + kBlock / 64 - 1) / (kBlock / 64);
+    hipLaunchKernelGGL(k_init, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(kBlock), 0, st, planes,
+                       L, key_init, thr_fill);
     return hipGetLastError();
 }
 
