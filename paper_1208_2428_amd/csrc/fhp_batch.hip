@@ -706,12 +706,13 @@ static_assert(sizeof(TileItem) <= sizeof(GroupDesc), "tiles use the group and wa
 // Tiles against bands, by the deepest launch (n_max steps) and the members'
 // words.  Launches of 10 steps and more step any batch faster as tiles
 // (random sides up to 2048, us per step at 16 steps, tiles and bands: 60
-// lattices 10.4 and 20.5, 512 64 and 81; with forcing 11.8 and 21.0, 73 and
+// lattices 9.7 and 20.5, 512 61 and 81; with forcing 10.5 and 21.0, 72 and
 // 109).  A launch of 5 to 9 steps recomputes and reloads more halo per step:
 // up to kTileBatchWords words, where a sweep has too few bands for two waves
-// per SIMD, tiles are faster (channels, 0.05 million words 1.8 and 19.5, 1.9
-// million 18.5 and 24.9), above it bands (3.5 million 32.8 and 27.9).
-constexpr uint64_t kTileBatchWords = 2500000;
+// per SIMD, tiles are faster (channels, 0.05 million words 1.9 and 19.6, 1.9
+// million 16.7 and 25.1), above it bands (3.5 million 28.5 and 27.5, 7.6
+// million 60 and 55).
+constexpr uint64_t kTileBatchWords = 3000000;
 constexpr uint32_t kTileBatchDeep = 10;
 
 // Decides between tiles and bands for sims[0..n) and launches of `n_min` to

@@ -46,18 +46,20 @@ inline uint32_t tiles_per_row(uint32_t C, uint32_t wd) {
 // workgroup's count rounded up to four, one per SIMD: 7 waves cost more than
 // 8) times the rows each holds, less those that no longer matter.
 //  - Workgroups that have their compute unit to themselves (all tiles in one
-//    round, or 1024 threads of two rows): 5 us + 0.36 us a row with one row
-//    per thread, 6.5 + 0.30 with two.
+//    round, or 1024 threads of two rows): 3.5 us and 0.15 per wave of a SIMD,
+//    and a step 0.1 us + 0.22 us a row with one row per thread; 5.5 us, 0.06
+//    + 0.25 with two.
 //  - Two workgroups per compute unit, one working while the other waits at its
-//    barrier: 4 us, and per round 3 us + 0.255 or 0.24 us a row (0.27 or 0.29
-//    where a single round starts them all together).
-// Fitted to launches of 20 lattices from 64^2 to 16384^2 (FHP-II with forcing;
-// FHP-III takes 1.7 times the arithmetic, no forcing 0.87).  Measured us per
-// step of the shape it picks, and of the fastest one found: 256^2 0.53, 0.53;
-// 1024^2 0.75, 0.74; 2048^2 1.02, 1.02; 4096^2 2.1, 2.1; 8192 x 8128 7.3, 7.2.
+//    barrier: 3 us, and per round 2.1 us + 0.225 or 0.212 us a row (0.235 or
+//    0.26 where a single round starts them all together).  Rounds end by
+//    halves, a workgroup per compute unit.
+// Fitted to launches of 22 lattices from 64^2 to 12288 x 8192 (FHP-II with
+// forcing; FHP-III takes 2.2 or 1.9 times the arithmetic, no forcing 0.87).  Measured
+// us per step of the shape it picks, and of the fastest one found: 256^2 0.52,
+// 0.52; 512^2 0.57, 0.58; 1024^2 0.67, 0.67; 3072^2 1.29, 1.33; 4096^2 1.81,
+// 1.76; 8192 x 8128 6.3, 6.8.
 inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool force, uint64_t steps) {
     TilePlan best{};
-    const double alu = (fhp3 ? 1.7 : 1.0) * (force ? 1.0 : 0.87);
     auto consider = [&](uint32_t R, uint32_t C, uint32_t threads, uint32_t n) {
         const uint32_t halo = tile_halo(n);
         // the most rows whose threads fit (an even number of waves for R = 1)
@@ -69,21 +71,24 @@ inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool
         const uint32_t rows = T + 2 * halo, waves = tile_threads(R, rows, C) / 64;
         const uint64_t grid = (uint64_t)ty * tiles_per_row(C, wd);
         const uint64_t per_cu = (grid + cus - 1) / cus;
-        // rows beyond those that still matter are skipped wave by wave
-        const double live = std::min(1.0, (double)(T + n - 1 + R) / rows);
+        // rows beyond those that still matter are skipped, wave by wave where
+        // a wave's rows are many (one word per thread)
+        const uint32_t whole = R == 1 ? std::min(128 / C, rows) : R;
+        const double live = std::min(1.0, (double)(T + n - 1 + whole) / rows);
+        const double alu = (fhp3 ? (R == 1 ? 2.2 : 1.9) : 1.0) * (force ? 1.0 : 0.87);
         const double row = live * ((waves + 3) / 4) * R;  // of one workgroup, on each SIMD
         // LDS: 160 KB hold two workgroups, but one of 1024 threads with R = 2
         // (and registers one of more than 768 with R = 1)
         const bool two = R == 1 ? threads <= (fhp3 ? 640u : 768u) : threads <= 512;
         double launch, step;
         if (per_cu == 1 || !two) {
-            launch = (R == 1 ? 5.0 : 6.5) * per_cu;
-            step = per_cu * std::max(row, (double)R) * (R == 1 ? 0.36 : 0.30) * alu;
+            launch = (R == 1 ? 3.5 + 0.15 * ((waves + 3) / 4) : 5.5) * per_cu;
+            step = per_cu * (R == 1 ? 0.1 + std::max(row, 1.0) * 0.22 * alu : 0.06 + std::max(row, 2.0) * 0.25 * alu);
         } else {
             const double x = (double)grid / (2.0 * cus);
-            const double rounds = x <= 1.0 ? 1.0 : x + 0.3;
-            launch = 4.0 + 3.0 * rounds;
-            const double c = x <= 1.0 ? (R == 1 ? 0.27 : 0.29) : (R == 1 ? 0.255 : 0.24);
+            const double rounds = x <= 1.0 ? 1.0 : 0.5 * (double)((grid + cus - 1) / cus) + 0.13;
+            launch = 3.0 + 2.1 * rounds;
+            const double c = x <= 1.0 ? (R == 1 ? 0.235 : 0.26) : (R == 1 ? 0.225 : 0.212);
             step = rounds * 2 * row * c * alu;
         }
         const uint64_t launches = (steps + n - 1) / n;
