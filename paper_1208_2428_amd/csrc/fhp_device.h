@@ -222,23 +222,26 @@ FHP_HD void collide_fhp3(const uint32_t a[7], uint32_t s, uint32_t chi, uint32_t
     E[1] = pair_flip(mux3(y1, q, D), r1, mux3(chi, b[2], b[0]));
     E[2] = xor3(E[0], E[1], q & x);
     // F and C: the class holding two (even: ge, odd: go); h1, h0 pick C's side.
-    // With two of three channels p, q', c of a class set, c is ~(p & q').
+    // With two of three channels p, q', c of a class set, c is ~(p & q').  R3
+    // is disjoint from both: with h1 and h0 set, its flip of the empty class is
+    // the other class's term below whatever the neighbours hold.
     const uint32_t g = F | C;
-    const uint32_t h1 = C & chi, h0 = C & ~chi;
+    const uint32_t h1 = lop3<(kA & kB) | kC>(C, chi, r3f), h0 = lop3<(kA & ~kB) | kC>(C, chi, r3f);
     const uint32_t g2[2] = {g & ce, g & co};
+    const uint32_t e2[2] = {g2[1] | ve, g2[0] | vo};
 #pragma unroll
     for (int j = 0; j < 6; j++) {
-        const uint32_t gs = g2[j & 1], gn = g2[1 - (j & 1)];
+        const uint32_t gs = g2[j & 1], gn = e2[j & 1];
         const uint32_t am = b[(j + 5) % 6], ap = b[(j + 1) % 6];
         const uint32_t p2 = b[(j + 2) % 6], m2 = b[(j + 4) % 6];
-        // two in the other class: F: A & B, C: chi ? B : A
+        // two in the other class: F: A & B, C: chi ? B : A; R3: 1
         const uint32_t u = lop3<(kA | kB) & kC>(am, h1, gn);
         const uint32_t wn = lop3<kA & (kB | kC)>(u, ap, h0);
         // two in this class: F: its particles, C: chi ? ~m2 : ~p2 -- of the
         // two terms at most one is set
         const uint32_t t1 = lop3<~kA & ~kB & kC & 0xFF>(p2, h1, gs);
         const uint32_t t0 = lop3<~kA & ~kB & kC & 0xFF>(m2, h0, gs);
-        o[j] = xor3(xor3(a[j], E[j % 3], (j & 1) ? vo : ve), wn, t1 ^ t0);
+        o[j] = xor3(xor3(a[j], E[j % 3], wn), t1, t0);
     }
     o[6] = a[6] ^ or3(r3f, F, C);
 }
