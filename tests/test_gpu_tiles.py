@@ -1,0 +1,208 @@
+"""The default routes -- tiled passes of one lattice, of a batch and of a pool,
+and the six-step sweep of large lattices -- bit for bit against single steps
+(depth 1) and the oracle, at the edges of tiles, rounds and launches."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1208_2428_amd import Batch, Pool, Sim
+from paper_1208_2428_amd import _binding as B
+from paper_1208_2428_amd import workloads as WL
+
+pytestmark = pytest.mark.gpu
+
+THREADS = oracle.default_threads()
+
+
+def sprinkle(W, H, frac, seed):
+    return (np.random.default_rng(seed).random((H, W)) < frac).astype(np.uint8)
+
+
+# (W, H): one word; rows that wrap within the halo; widths around whole waves
+# and around the widest full rows; one and two words per thread, one and two
+# workgroups per compute unit.
+SHAPES = [(64, 2), (64, 4), (64, 66), (128, 10), (320, 96), (320, 254), (1984, 130), (2048, 36),
+          (4032, 22), (4096, 18), (4160, 26), (4224, 38), (1024, 512), (512, 2050), (2304, 2306),
+          (4096, 4096), (6016, 6002)]
+
+
+@pytest.mark.parametrize("rules", [oracle.RULES_FHP1, oracle.RULES_FHP2, oracle.RULES_FHP3])
+@pytest.mark.parametrize("W,H", SHAPES)
+def test_tiled_passes_match_single_steps(W, H, rules):
+    k = SHAPES.index((W, H)) + 3 * rules
+    for force, walls, frac, chir in ((0.0, False, 0.0, 0), (1e-2, True, 0.05, k % 3)):
+        print("tiles", W, H, rules, force, walls, frac, chir, flush=True)
+        solid = sprinkle(W, H, frac, k) if frac else None
+        kw = dict(seed=41 + k, fill=0.3, force_rate=force, walls=walls, solid=solid, chirality=chir,
+                  rules=rules)
+        a, b = Sim(W, H, **kw), Sim(W, H, **kw, depth=1)
+        for n in (2, 3, 31, 35):
+            a.step(n)
+            b.step(n)
+            assert a.digest() == b.digest(), (n, a.t)
+        np.testing.assert_array_equal(a.get_state(), b.get_state())
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("W,H,walls,chir", [(64, 34, False, 0), (320, 70, True, 1), (1088, 46, True, 0)])
+def test_tiled_passes_match_oracle(W, H, walls, chir):
+    st = WL.random_states(np.random.default_rng(W), H, W, p=0.4, solid_frac=0.05)
+    if walls:
+        st[0] |= 0x80
+        st[-1] |= 0x80
+    s = Sim(W, H, seed=7, force_rate=5e-3, walls=walls, chirality=chir)
+    s.set_state(st, t=9)
+    s.step(67)
+    ref, _ = oracle.run(st, 9, 67, 7, 5e-3, chir_mode=chir, threads=THREADS)
+    np.testing.assert_array_equal(s.get_state(), ref)
+    s.close()
+
+
+@pytest.mark.parametrize("W,H,rules", [(320, 96, 0), (2560, 2562, 2)])
+def test_tensor_steps_match_single_steps(W, H, rules):
+    lib = B.load()
+    p, _ = B.make_params(W, H, seed=3, force_rate=1e-3, walls=True, rules=rules)
+    g = torch.Generator(device="cuda").manual_seed(W)
+    src = torch.randint(-2**62, 2**62, (7, H, W // 64), dtype=torch.int64, device="cuda", generator=g)
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    out = []
+    for depth in (0, 1):
+        dst = torch.empty_like(src)
+        B.check(lib.fhp_step_noalloc(ctypes.byref(p), ctypes.c_void_p(src.data_ptr()),
+                                     ctypes.c_void_p(dst.data_ptr()), None, 5, 41, depth, st))
+        out.append(dst)
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("W,H,rules,masked", [(16384, 9730, 1, True), (16384, 9730, 0, False),
+                                              (12352, 12290, 2, True)])
+def test_default_sweep_of_large_lattices(W, H, rules, masked):
+    """Lattices beyond the tiles' range: six steps per pass (FHP-III three),
+    bands that do not divide the height, a rest of single passes."""
+    solid = None
+    if masked:
+        solid = np.zeros((H, W), dtype=np.uint8)
+        solid[::97, ::89] = 1
+    kw = dict(seed=5, fill=0.3, force_rate=1e-3 if masked else 0.0, walls=masked, solid=solid, rules=rules)
+    a, b = Sim(W, H, **kw), Sim(W, H, **kw, depth=1)
+    for n in (6, 14):
+        a.step(n)
+        b.step(n)
+        assert a.digest() == b.digest(), n
+    a.close()
+    b.close()
+
+
+def batch_members(rules, solid):
+    return [dict(width=W, height=H, seed=60 + k, fill=0.3, force_rate=1e-2 if k % 2 else 0.0, rules=rules,
+                 walls=bool(solid and k % 3 == 0), chirality=k % 3 if k > 3 else 0,
+                 solid=sprinkle(W, H, 0.05, k) if solid and k % 2 == 0 else None)
+            for k, (W, H) in enumerate([(64, 8), (64, 66), (320, 34), (2048, 130), (4096, 20), (4160, 22),
+                                        (704, 300), (64, 1000)])]
+
+
+@pytest.mark.parametrize("rules", [oracle.RULES_FHP1, oracle.RULES_FHP2, oracle.RULES_FHP3])
+@pytest.mark.parametrize("solid", [False, True])
+def test_batch_tiles_match_single_steps(rules, solid):
+    ms = batch_members(rules, solid)
+    b = Batch(ms)
+    ref = [Sim(**m, depth=1) for m in ms]
+    for n in (16, 1, 35, 5):
+        b.step(n)
+        for s in ref:
+            s.step(n)
+        # a member stepped alone in between leaves the batch's tables stale
+        b.members[n % len(ms)].step(n)
+        ref[n % len(ms)].step(n)
+    b.sync()
+    for m, s in zip(b.members, ref):
+        assert m.digest() == s.digest() and m.t == s.t
+    # through bands and back
+    b.set_tiling(depth=3)
+    b.step(7)
+    b.set_tiling()
+    b.step(18)
+    for m, s in zip(b.members, ref):
+        s.step(25)
+        assert m.digest() == s.digest()
+        s.close()
+    b.close()
+
+
+def test_large_batch_between_tiles_and_bands():
+    """More words than tiles take for shallow calls: deep, shallow, shallow, deep."""
+    ms = [dict(width=8192, height=8192, seed=k, fill=0.3) for k in range(3)]
+    b = Batch(ms)
+    ref = [Sim(**m, depth=1) for m in ms]
+    for n in (20, 4, 4, 3, 32, 9):
+        b.step(n)
+        for m, s in zip(b.members, ref):
+            s.step(n)
+            assert m.digest() == s.digest(), n
+    for s in ref:
+        s.close()
+    b.close()
+
+
+@pytest.mark.parametrize("passes", [1, 2, 6])
+def test_pool_tiles_end_every_job_at_its_own_step(passes):
+    """Jobs whose lengths leave every remainder of a tick, joining and leaving."""
+    pool = Pool(Pool.arena_bytes_for(12, 4096, 64 << 20), max_slots=12, max_bands=4096, group_threads=128)
+    jobs = [(n, dict(width=64 * (1 + k % 5), height=8 + 26 * k, seed=90 + k, fill=0.3,
+                     force_rate=1e-3 if k % 2 else 0.0, walls=k % 3 == 0))
+            for k, n in enumerate((1, 4, 5, 6, 9, 14, 30, 31, 35, 64))]
+    slot_job = {pool.admit(n, **p): k for k, (n, p) in enumerate(jobs[:6])}
+    waiting, got = list(range(6, len(jobs))), {}
+    while slot_job:
+        pool.tick(passes)
+        for slot in pool.done():
+            k = slot_job.pop(slot)
+            got[k] = pool.member(slot).get_state()
+            pool.release(slot)
+            if waiting:
+                j = waiting.pop(0)
+                slot_job[pool.admit(jobs[j][0], **jobs[j][1])] = j
+    pool.close()
+    assert sorted(got) == list(range(len(jobs)))
+    for k, (n, p) in enumerate(jobs):
+        s = Sim(**p, depth=1)
+        s.step(n)
+        np.testing.assert_array_equal(got[k], s.get_state(), err_msg=str((k, n, p)))
+        s.close()
+
+
+@pytest.mark.parametrize("W,H", [(64, 2), (64, 34), (192, 66), (4096, 258)])
+def test_state_conversion_edges(W, H):
+    """Bytes to planes and back, one obstacle anywhere (or none) noticed."""
+    for at in (None, (0, 0), (H - 1, W - 1), (H // 2, 17 % W)):
+        st = np.random.default_rng(W + H).integers(0, 128, (H, W), dtype=np.uint8)
+        if at:
+            st[at] = 0x80
+        s = Sim(W, H, seed=1)
+        s.set_state(st)
+        np.testing.assert_array_equal(s.get_state(), st)
+        s.step(4)
+        ref, _ = oracle.run(st, 0, 4, 1, 0.0, threads=THREADS)
+        np.testing.assert_array_equal(s.get_state(), ref)
+        s.close()
+
+
+@pytest.mark.parametrize("offset", [0, 1, 4095])
+def test_download_while_steps_are_queued(offset):
+    """The state into fresh, unaligned host memory behind a queue of steps."""
+    W, H = 4096, 1026
+    a, b = Sim(W, H, seed=2, fill=0.3), Sim(W, H, seed=2, fill=0.3, depth=1)
+    b.step(600)
+    want = b.get_state()
+    a.step(600)
+    raw = np.empty(W * H + offset + 64, dtype=np.uint8)
+    raw[-64:] = 0xA5
+    B.check(a._lib.fhp_get_state(a._handle(), ctypes.c_void_p(raw.ctypes.data + offset), W * H))
+    np.testing.assert_array_equal(raw[offset:offset + W * H].reshape(H, W), want)
+    assert (raw[-64:] == 0xA5).all()
+    a.close()
+    b.close()
