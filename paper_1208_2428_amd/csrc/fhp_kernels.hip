@@ -173,8 +173,10 @@ __global__ void __launch_bounds__(kBlock) k_observe_global(const uint64_t* __res
 // Block sums over b x b node blocks: one thread per output block (by, bx),
 // for block rows brow0 .. brow0 + brows - 1 and block columns bx0 .. bx0 +
 // nbx - 1, written row-major (nbx blocks per row).  b divides 64 (a block is
-// a b-bit field of one word) or is a multiple of 64 (a block spans b/64
-// whole words).
+// a b-bit field of one half of a word) or is a multiple of 64 (a block spans
+// b/64 whole words).  A thread's loads are a serial chain of b rows: four rows'
+// are in flight at once, and the sums follow from seven counts at its end (16 x
+// 16 blocks of 2048^2, the call with its copy: 38.6 -> 36 us).
 __global__ void __launch_bounds__(kBlock) k_observe_blocks(const uint64_t* __restrict__ planes,
                                                            Lattice L, uint32_t b, uint32_t brow0,
                                                            uint32_t brows, uint32_t bx0, uint32_t nbx,
@@ -183,32 +185,25 @@ __global__ void __launch_bounds__(kBlock) k_observe_blocks(const uint64_t* __res
     if (o >= (size_t)brows * nbx) return;
     const uint32_t by = brow0 + (uint32_t)(o / nbx), bx = bx0 + (uint32_t)(o % nbx);
     const uint32_t y0 = by * b, y1 = min(L.H, y0 + b);
-    int32_t rho = 0, px = 0, py = 0;
-    uint32_t w0, w1;
-    uint64_t field;
+    int32_t n[7] = {0};
     if (b < 64) {
-        w0 = (bx * b) >> 6;
-        w1 = w0 + 1;
-        field = ((1ull << b) - 1) << ((bx * b) & 63);
+        const uint32_t* half = (const uint32_t*)planes + (bx * b >> 5);
+        const uint32_t field = (b < 32 ? (1u << b) - 1 : ~0u) << (bx * b & 31);
+#pragma unroll 4
+        for (uint32_t y = y0; y < y1; y++)
+#pragma unroll
+            for (int c = 0; c < 7; c++) n[c] += __popc(half[2 * (c * L.ps + (size_t)y * L.wd)] & field);
     } else {
-        w0 = bx * (b >> 6);
-        w1 = min(L.wd, w0 + (b >> 6));
-        field = ~0ull;
+        const uint32_t w0 = bx * (b >> 6), w1 = min(L.wd, w0 + (b >> 6));
+        for (uint32_t y = y0; y < y1; y++)
+            for (uint32_t w = w0; w < w1; w++)
+#pragma unroll
+                for (int c = 0; c < 7; c++) n[c] += __popcll(planes[c * L.ps + (size_t)y * L.wd + w]);
     }
-    for (uint32_t y = y0; y < y1; y++)
-        for (uint32_t w = w0; w < w1; w++) {
-            const size_t idx = (size_t)y * L.wd + w;
-            for (int c = 0; c < 7; c++) {
-                const int32_t k = __popcll(planes[(size_t)c * L.ps + idx] & field);
-                rho += k;
-                px += kPx[c] * k;
-                py += kPy[c] * k;
-            }
-        }
     int32_t* dst = out + o * 3;
-    dst[0] = rho;
-    dst[1] = px;
-    dst[2] = py;
+    dst[0] = n[0] + n[1] + n[2] + n[3] + n[4] + n[5] + n[6];
+    dst[1] = n[1] + n[3] - n[0] - n[4] + 2 * (n[2] - n[5]);
+    dst[2] = n[3] + n[4] - n[0] - n[1];
 }
 
 // Row sums of (rho, p_x, p_y) for rows row0 .. row0 + rows - 1: one workgroup
