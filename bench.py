@@ -41,12 +41,17 @@ def golden_digest(name: str, t: int):
     return None
 
 
+def profile_note(name: str, depth: int) -> str:
+    """The note under profiles/ of a workload's pass of `depth` steps."""
+    return os.path.join(ROOT, "profiles", f"k_stepk_{name}{'' if depth <= 5 else f'-depth{depth}'}.md")
+
+
 def recorded_traffic(name: str, depth: int):
     """HBM bytes per launch from the rocprofv3 counters recorded under
     profiles/ for this kernel, or None if they were taken on other kernel
     sources or another depth."""
     from paper_1208_2428_amd import profsum
-    path = os.path.join(ROOT, "profiles", f"k_stepk_{name}.md")
+    path = profile_note(name, depth)
     traffic, src, rec_depth = profsum.recorded_traffic(path)
     if traffic is None or depth != rec_depth or src != profsum.kernel_source_hash():
         return None
@@ -149,12 +154,22 @@ def recorded_valu(name: str, depth: int):
     pass recorded under profiles/, if it was taken on these kernel sources at
     this depth."""
     from paper_1208_2428_amd import profsum
-    path = os.path.join(ROOT, "profiles", f"k_stepk_{name}.md")
+    path = profile_note(name, depth)
     _, src, rec_depth = profsum.recorded_traffic(path)
     insts = profsum.recorded_value(path, "valu_insts_per_launch")
     if insts is None or depth != rec_depth or src != profsum.kernel_source_hash():
         return None
     return insts
+
+
+def steps_per_launch(sim, rules: int, depth: int, band: int) -> int:
+    """Steps of one launch of a large lattice's sweep.  With depth and band left
+    to the library it takes six steps per pass (FHP-III three) where its
+    nominal default depth is the deepest one; otherwise the depth itself."""
+    from paper_1208_2428_amd import _binding as B
+    if rules == B.RULES_FHP3:
+        return min(sim.depth, 3)
+    return 6 if not depth and not band and sim.depth == B.MAX_DEPTH else sim.depth
 
 
 def depth_sweep(wl, mask, min_seconds: float, last: int | None = None):
@@ -163,6 +178,7 @@ def depth_sweep(wl, mask, min_seconds: float, last: int | None = None):
     fraction of 14/K bits per node-step falls with K by construction); depth
     `last` is measured last."""
     from paper_1208_2428_amd import _binding as B
+    last = last if last and last <= B.MAX_DEPTH else None
     ks = [k for k in range(1, B.MAX_DEPTH + 1) if k != last] + ([last] if last else [])
     out = []
     for k in ks:
@@ -176,7 +192,7 @@ def depth_sweep(wl, mask, min_seconds: float, last: int | None = None):
 
 def plain_rate(wl, mask, depth: int, min_seconds: float = 0.1):
     """(node updates/s, steps timed) of the single-lattice kernel at depth
-    `depth`: a short untimed run sizes the measurement, which is then timed
+    `depth` (0: the library's default passes): a short untimed run sizes the measurement, which is then timed
     with HIP events on the stream the kernels run on over at least
     `min_seconds`, after an untimed run of the same length."""
     import torch
@@ -184,9 +200,10 @@ def plain_rate(wl, mask, depth: int, min_seconds: float = 0.1):
     from paper_1208_2428_amd import Sim
     from paper_1208_2428_amd.autotune import time_steps
     sim = Sim(**wl.params(), solid=mask, depth=depth)
-    probe = time_steps(sim.step, torch.cuda.current_stream(), 12 * depth, 1)
-    n = max(depth, int(min_seconds / probe) + 1)
-    n = (n + depth - 1) // depth * depth
+    per = depth or 6
+    probe = time_steps(sim.step, torch.cuda.current_stream(), 12 * per, 1)
+    n = max(per, int(min_seconds / probe) + 1)
+    n = (n + per - 1) // per * per
     per_step = time_steps(sim.step, torch.cuda.current_stream(), n, 1)
     sim.close()
     return wl.width * wl.height / per_step, n
@@ -209,8 +226,8 @@ def golden_ensemble():
 
 def batched_leg(args, plain_at):
     """512 uneven lattices in one batch vs the plain single-lattice kernel at
-    the same depth; every member's digest against the same lattice stepped
-    alone and against the oracle's."""
+    the same depth (0: both with the library's default passes); every member's
+    digest against the same lattice stepped alone and against the oracle's."""
     from paper_1208_2428_amd import ensemble
     params = ensemble.ensemble_params()
     log(f"bench: ensemble of {len(params)} lattices, {args.ensemble_steps} steps (tuning first)")
@@ -239,8 +256,9 @@ def batched_leg(args, plain_at):
 
 def rules_leg(args, wl, mask, plain_at):
     """The headline workload under the other rule sets (FHP-I, FHP-III), each
-    at its default depth: throughput (HIP events) and per-launch HBM roofline
-    fraction, against FHP-II at the same depth."""
+    with the library's default passes: throughput (HIP events) and per-launch
+    HBM roofline fraction, against FHP-II at the same depth (FHP-I: the same
+    default passes)."""
     import torch
 
     from paper_1208_2428_amd import Sim
@@ -249,17 +267,16 @@ def rules_leg(args, wl, mask, plain_at):
     stream = torch.cuda.current_stream()
     nodes = wl.width * wl.height
     out = {}
-    for name, rules, max_depth in (("fhp1", B.RULES_FHP1, B.MAX_DEPTH), ("fhp3", B.RULES_FHP3, 3)):
+    for name, rules in (("fhp1", B.RULES_FHP1), ("fhp3", B.RULES_FHP3)):
         sim = Sim(**wl.params(), solid=mask, rules=rules)
-        depth = min(sim.depth, max_depth)  # steps per launch
-        sim.depth = depth
+        depth = steps_per_launch(sim, rules, 0, 0)
         steps = args.rules_steps - args.rules_steps % depth
         per_step = time_steps(sim.step, stream, steps, 1)
         launch_s = launch_seconds(sim, stream, depth, 200)
         sim.close()
         achieved = PLANE_BITS * nodes / 8 / launch_s / 1e9
         value = nodes / per_step
-        fhp2 = plain_at(depth)
+        fhp2 = plain_at(depth if depth <= B.MAX_DEPTH else 0)
         out[name] = {"value": value, "unit": "node-updates/s", "depth": depth, "steps": steps,
                      "fhp2_same_depth": fhp2, "ratio_vs_fhp2": value / fhp2,
                      "kernel_us": launch_s * 1e6, "roofline_frac": achieved / HBM_PEAK_GBS}
@@ -421,10 +438,10 @@ def small_config(name: str, min_seconds: float):
     e1.record(stream)
     e1.synchronize()
     sec = e0.elapsed_time(e1) / 1e3
-    depth = sim.depth
+    depth = sim.depth  # nominal: lattices of this size step as tiles by default
     sim.close()
     value = wl.width * wl.height * wl.steps * runs / sec
-    log(f"bench: {name}: {value:.3e} node-updates/s at depth {depth} "
+    log(f"bench: {name}: {value:.3e} node-updates/s with the default passes "
         f"({runs} runs of {wl.steps} steps); digest at t={wl.steps} "
         f"{'matches' if parity else 'DIFFERS FROM' if parity is False else 'has no'} oracle")
     return {"value": value, "unit": "node-updates/s", "width": wl.width, "height": wl.height,
@@ -476,6 +493,7 @@ def main() -> int:
 
     import torch
 
+    from paper_1208_2428_amd import _binding as B
     from paper_1208_2428_amd import Sim
     from paper_1208_2428_amd import workloads as WL
 
@@ -494,8 +512,8 @@ def main() -> int:
     # the warm-up and the timed steps come right after them, as in the middle
     # of a long run.
     warm = Sim(**wl.params(), solid=mask, depth=args.depth, band=args.band)
-    depth, band = warm.depth, warm.band
-    sim = Sim(**wl.params(), solid=mask, depth=depth, band=args.band)
+    depth, band = steps_per_launch(warm, B.RULES_FHP2, args.depth, args.band), warm.band
+    sim = Sim(**wl.params(), solid=mask, depth=args.depth, band=args.band)
     ceiling = None
     if not args.no_ceiling:
         ceiling = memory_ceiling(wl, depth, band, has_mask=mask is not None)
@@ -589,6 +607,8 @@ def main() -> int:
 
     if not args.no_configs:
         out["configs"] = {n: small_config(n, 0.1) for n in ("torus-256", "channel-4096")}
+    if depth > B.MAX_DEPTH:  # what the timed lattice ran
+        plain[0] = out["events_value"]
     if not args.no_ensemble:
         out["batched"] = batched_leg(args, plain_at)
     if not args.no_serve:

@@ -144,7 +144,11 @@ int fhp_create(const fhp_params *p, void *dev_ws, size_t ws_bytes, void *hip_str
 
 /* Temporal-block depth k (1..FHP_MAX_DEPTH): fhp_step runs k steps per pass over
  * HBM (the last pass of a call may be shorter).  0 selects the library's default
- * for this lattice: 3 where the lattice is too small to give every SIMD of the
+ * for this lattice.  While depth and band are both the defaults, fhp_step takes
+ * what it finds fastest: tiled launches of up to 32 steps on lattices of up to
+ * 12288^2 nodes, on larger ones passes of 6 steps (FHP-III 3) in bands of its
+ * own choice.  fhp_get_depth then returns the nominal depth, which a pass has
+ * when a band is set: 3 where the lattice is too small to give every SIMD of the
  * device two waves (as for 4096 x 4096 on 256 compute units), 4 where the
  * default band (fhp_get_band) is 8 rows or fewer, FHP_MAX_DEPTH otherwise.
  * k > 1 needs width <= 32768.
@@ -159,7 +163,8 @@ int fhp_get_depth(const fhp_sim *s, uint32_t *k);
  * K halo rows above and below it.  Results do not depend on it.  FHP_E_INVAL
  * above the lattice height. */
 int fhp_set_band(fhp_sim *s, uint32_t rows);
-/* The band height fhp_step uses: the one set, or the default it resolves to. */
+/* The band height set, or the default it resolves to (see fhp_set_depth for what
+ * fhp_step takes while depth and band are both the defaults). */
 int fhp_get_band(const fhp_sim *s, uint32_t *rows);
 
 /* Advances n steps (Sec. 2: motion then scattering, each step).  Asynchronous:
@@ -195,7 +200,8 @@ void fhp_destroy(fhp_sim *s);
  * advanced together by one persistent kernel.  Lattices are cut into bands of
  * rows; bands of lattices with the same row width are packed side by side into
  * one workgroup, and a persistent grid takes (pass, band group) work items from
- * a device counter.  With more than one pass per launch, a band waits for its
+ * a device counter.  With the default tiling throughout, a batch is cut into
+ * tiles instead, one launch per up to 16 steps, where that is faster.  With more than one pass per launch, a band waits for its
  * two neighbouring bands' previous pass (per-band counters on the device).
  * Each member's results are identical to those of a standalone simulation with
  * the same parameters (Sec. 2 model; the same readings as above).
@@ -217,7 +223,8 @@ int fhp_batch_create(const fhp_params *ps, uint32_t n, void *dev_ws, size_t ws_b
                      void *hip_stream, fhp_batch **out);
 
 /* Tiling of the batch kernel: depth K (0 = FHP_BATCH_MAX_DEPTH), target band height
- * (0 = from occupancy: the largest even target up to 32 whose bands give every
+ * (all four at their defaults, 0, 0, 0 and 1: tiles where they are faster;
+ * 0 = from occupancy: the largest even target up to 32 whose bands give every
  * SIMD two waves, else one, else the one with most waves; per member the
  * largest even divisor of H not above it and >= K),
  * threads per workgroup (0 = smallest multiple of 64 holding the widest row),
@@ -272,7 +279,8 @@ int fhp_pool_create(void *dev_arena, size_t arena_bytes, uint32_t max_slots, uin
 
 /* Depth (0 = FHP_BATCH_MAX_DEPTH), target band height (0 = 32) and workgroup size
  * (0 = smallest that holds the widest row) of the pool's launches; only while
- * the pool is empty. */
+ * the pool is empty.  While the band is the default, a tick of up to 32 steps
+ * may run as one launch of tiles, whatever depth and workgroup size. */
 int fhp_pool_set_tiling(fhp_pool *pl, uint32_t depth, uint32_t band, uint32_t group_threads);
 
 /* Rule set (FHP_RULES_*) of every job of the pool, FHP-II until set; only
@@ -348,7 +356,8 @@ void fhp_pool_destroy(fhp_pool *pl);
  *   dev_solid: device, H * (W/64) uint64 words, bit set = obstacle node, or
  *              NULL for none; FHP_WALLS_CHANNEL adds rows 0 and H-1;
  *   t:         steps already done (the hash counters use it);
- *   depth:     steps per pass as for fhp_set_depth (0 = default).
+ *   depth:     steps per pass as for fhp_set_depth (0 = default: tiled
+ *              launches of up to 32 steps).
  * All buffers stay the caller's and must stay alive until the work has run.
  * Errors: FHP_E_INVAL for bad parameters or pointers, FHP_E_NOMEM for a state
  * above FHP_NOALLOC_MAX_STATE_BYTES, FHP_E_STATE if t + n would reach 2^24,

@@ -20,7 +20,7 @@ HIPCC_FLAGS = [
 ]
 
 
-# Per-source extra flags.  The depth-5 pass of wide lattices is scheduled for
+# Per-source extra flags.  The depth-5 and depth-6 passes of wide lattices are scheduled for
 # instruction-level parallelism (see fhp_stepk_k5.hip).
 FILE_FLAGS = {
     "fhp_stepk_k5.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],

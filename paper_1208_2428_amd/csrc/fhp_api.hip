@@ -172,9 +172,10 @@ uint32_t default_depth(uint32_t H, uint32_t wd, uint32_t simds) {
 
 // Tiles against sweeping bands (default depth and band): lattices of up to
 // kTileNodes nodes run tiled passes.  Measured us per step, tiles and sweep
-// (default bands; best bands): 8960 x 8192 8.0, 12.8; 12288 x 8192 10.0, 13.0;
-// 10.8; 12288^2 14.5, 17.5; 14.6; 16384 x 12288 18.8, 18.2; 17.6; 16384^2 25,
-// 22.  FHP-III the same way: 12288 x 8192 16.7, 20.8; 16384^2 49, 38.
+// (default bands; best bands): 8960 x 8192 7.0, 12.8; 12288 x 8192 9.0, 13.0;
+// 10.8; 12288^2 13.4, 17.5; 14.6.  Above, a sweep's bands give every SIMD two
+// waves and its bytes per step are fewer: 16384 x 12288 17.6 (tiles 18 by the
+// rate of 12288^2), 16384^2 20.5 (24).
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) {
     if (n < 2 || (uint64_t)L.W * L.H > kTileNodes) return TilePlan{};
     return tile_plan(L.H, L.wd, simds / 4, D.rules == FHP_RULES_FHP3, D.thr_force != 0, n);

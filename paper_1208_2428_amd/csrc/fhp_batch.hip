@@ -23,6 +23,10 @@
 // host reports an error.  The last workgroup to leave advances every member's
 // time and buffer index and resets the counters, so a launch can be replayed
 // from a graph without host work in between.
+//
+// With the default tiling, batches and pools step as tiles of all members
+// instead (k_tiles, fhp_tile.h), one ordinary launch per up to 16 steps or per
+// tick; engine_tiles says where.
 #include <stdlib.h>
 #include <string.h>
 

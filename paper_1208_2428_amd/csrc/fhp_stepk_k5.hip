@@ -6,7 +6,8 @@
 // faster on 16384^2 at the same two waves per SIMD but 4% slower for the
 // depth-4 and one-wave passes of smaller lattices.  Depth 6 (246 VGPRs; depth
 // 7 spills with obstacles) moves 14% fewer bytes per step for 3% more halo
-// work: 16384^2 with obstacles 22.35 -> 21.07 us per step, without 21.8 -> 20.3.
+// work: 16384^2 with obstacles and forcing 22.4 -> 21.0 us per step (a launch:
+// 126 us, VALU busy 69%, the accesses alone 76 us), without both 21.8 -> 18.4.
 #include "fhp_stepk.h"
 
 namespace fhp {

@@ -14,11 +14,12 @@
 // What bounds it.  A step takes a wave about 120 VALU instructions per word
 // (FHP-II with forcing), 4.9 cycles each with four waves per SIMD, and the
 // barrier between publishing and reading, which leaves the SIMD idle unless
-// another workgroup has work; per launch about 4.5 us of launch, loads and
-// stores.  The sweep (3 steps per launch on these lattices) pays those 4.5 us
-// and the latency of its level chain every 3 steps: 256^2 1.68 -> 0.54 us per
-// step, 1024^2 2.0 -> 0.91, 2048^2 2.1 -> 1.17, 4096^2 2.9 -> 2.2,
-// 8192 x 8128 10.1 -> 8.1 (12288 x 8192 and larger stay with the sweep).
+// another workgroup has work; per launch 3 to 5 us of launch, loads and
+// stores (an empty launch takes 1.7).  The sweep (3 to 5 steps per launch on
+// these lattices) pays those and the latency of its level chain every few
+// steps: 256^2 1.68 -> 0.52 us per step, 1024^2 2.0 -> 0.67, 2048^2 2.1 ->
+// 0.83, 4096^2 2.9 -> 1.8, 8192 x 8128 10.1 -> 6.2, 12288 x 8192 12.8 -> 9.0
+// (lattices above 12288^2 nodes stay with the sweep).
 //
 // Horizontal neighbours are LDS entries of the same row, so any row width
 // packs its threads densely; vertical ones are entries of the rows above and
@@ -26,8 +27,9 @@
 // planes shift; the even rows' threads fill the first waves and the odd rows'
 // the others, so that the parity is uniform in a wave.  Two words per thread
 // (an even row and the odd one below) halve the barriers and a quarter of the
-// LDS accesses per word, 0.26 instead of 0.36 us per step and wave-row of a
-// SIMD, and need tiles of twice the rows: better from about 3000^2 on.
+// LDS accesses per word (a step of four waves per SIMD of each takes 0.9 us
+// with one word, 1.7 with two), and need tiles of twice the rows: better from
+// about 3000^2 on.
 #pragma once
 
 #include "fhp_device.h"
@@ -73,7 +75,8 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgc
 
 // Tile of workgroup b of nb.  Workgroups go round-robin to the eight dies (b to
 // b mod 8); die x takes the x-th contiguous run of tiles, so that the lines a
-// tile shares with its neighbours come through one L2.
+// tile shares with its neighbours come through one L2: launches of one step
+// 2048^2 9.0 -> 4.5 us, 4096^2 12.0 -> 7.4, 8192 x 8128 46 -> 25.
 __device__ __forceinline__ uint32_t tile_of(uint32_t b, uint32_t nb) {
     const uint32_t q = nb >> 3, r = nb & 7, x = b & 7;
     return x * q + min(x, r) + (b >> 3);

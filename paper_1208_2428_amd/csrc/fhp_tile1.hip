@@ -43,7 +43,7 @@ hipError_t launch_tile(const TilePlan& P, uint32_t steps, const uint64_t* in, ui
     const uint32_t rows = a.T + 2 * a.halo;
     const uint32_t nt = tile_threads(P.R, rows, P.C);
     const uint64_t grid = (uint64_t)((L.H + a.T - 1) / a.T) * a.tiles_x;
-    if (grid > 0x7fffffffull) return hipErrorInvalidValue;
+    if (nt > kTileMaxThreads || grid > 0x7fffffffull) return hipErrorInvalidValue;
     a.split = nt / 2;
     const bool force = D.thr_force != 0;
     if (P.R == 1) return launch_tiles_1((uint32_t)grid, nt, force, D.rules, in, out, L.S, a, st);
