@@ -24,6 +24,10 @@ HIPCC_FLAGS = [
 # instruction-level parallelism (see fhp_stepk_k5.hip).
 FILE_FLAGS = {
     "fhp_stepk_k5.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    # the tiled passes: why, in each file
+    "fhp_tile1.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
+    "fhp_tile2.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-minreg"],
+    "fhp_tile_batch.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-minreg"],
 }
 
 

@@ -443,10 +443,13 @@ hipError_t launch_tile2(uint32_t grid, uint32_t nt, const uint64_t* in, uint64_t
 
 }  // namespace
 
-// The kernels of one and of two words per thread (fhp_tile1.hip,
-// fhp_tile2.hip: two translation units, so that they compile in parallel).
+// The kernels of one and of two words per thread (fhp_tile1.hip and
+// fhp_tile1_fhp3.hip, fhp_tile2.hip: translation units of their own, which
+// compile in parallel and under schedules of their own).
 hipError_t launch_tiles_1(uint32_t grid, uint32_t nt, bool force, uint32_t rules, const uint64_t* in,
                           uint64_t* out, const uint64_t* S, const TileArgs& a, hipStream_t st);
+hipError_t launch_tiles_1_fhp3(uint32_t grid, uint32_t nt, bool force, const uint64_t* in, uint64_t* out,
+                               const uint64_t* S, const TileArgs& a, hipStream_t st);
 hipError_t launch_tiles_2(uint32_t grid, uint32_t nt, bool force, uint32_t rules, const uint64_t* in,
                           uint64_t* out, const uint64_t* S, const TileArgs& a, hipStream_t st);
 // Tiles of many lattices (fhp_tile_batch.hip); solid: any lattice has
