@@ -707,17 +707,24 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
 static_assert(sizeof(TileMember) <= sizeof(MemberDesc), "tile members use the member table's memory");
 static_assert(sizeof(TileItem) <= sizeof(GroupDesc), "tiles use the group and wave tables' memory");
 
-// Tiles against bands, by the deepest launch (n_max steps) and the members'
+constexpr uint32_t kTileBatchDeep = 10;
+
+// Tiles against bands, by the shallowest launch (n_min steps) and the members'
 // words.  Launches of 10 steps and more step any batch faster as tiles
 // (random sides up to 2048, us per step at 16 steps, tiles and bands: 60
 // lattices 9.7 and 20.5, 512 61 and 81; with forcing 10.5 and 21.0, 72 and
-// 109).  A launch of 5 to 9 steps recomputes and reloads more halo per step:
-// up to kTileBatchWords words, where a sweep has too few bands for two waves
-// per SIMD, tiles are faster (channels, 0.05 million words 1.9 and 19.6, 1.9
-// million 16.7 and 25.1), above it bands (3.5 million 28.5 and 27.5, 7.6
-// million 60 and 55).
-constexpr uint64_t kTileBatchWords = 3000000;
-constexpr uint32_t kTileBatchDeep = 10;
+// 109).  A launch of 5 to 9 steps recomputes and reloads more halo per step.
+// There a sweep takes what whole rounds of its bands take (two waves per SIMD,
+// 32 rows of 64 words each: kBandRoundWords), however empty they are: tiles
+// are faster unless a round is nearly full, or from 1.2 rounds on (channels,
+// million words: 0.05 1.9 and 19.6, 1.9 16.7 and 25.1, 2.5 22 and 27; 3.2 27.3 and
+// 27.1, 3.5 28.4 and 27.7; 3.9 31 and 36, 4.6 36 and 48, 4.9 39.8 and 39.9; 7.6
+// 60 and 55).
+constexpr uint64_t kBandRoundWords = 2ull * 1024 * 64 * 32;
+bool bands_take(uint64_t words, uint32_t n_min) {
+    const double x = (double)words / kBandRoundWords;
+    return n_min < kTileBatchDeep && ((x > 0.73 && x <= 0.9) || x > 1.19);
+}
 
 // Decides between tiles and bands for sims[0..n) and launches of `n_min` to
 // `n_max` steps and, for tiles, builds and uploads the tables.  limit: steps
@@ -731,7 +738,7 @@ int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_
         words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
         if ((uint64_t)sims[i]->L.W * sims[i]->L.H > kTileNodes) return FHP_OK;
     }
-    if (words > kTileBatchWords && n_min < kTileBatchDeep) return FHP_OK;
+    if (bands_take(words, n_min)) return FHP_OK;
     std::vector<TileShape> shapes(n);
     uint64_t items = 0;
     for (uint32_t i = 0; i < n; i++) {
@@ -1038,7 +1045,7 @@ int batch_step_tiles(fhp_batch* b, uint64_t n) {
     // single one does not change tables.
     uint64_t words = 0;
     for (uint32_t i = 0; i < b->n; i++) words += (uint64_t)b->sims[i].L.H * b->sims[i].L.wd;
-    const bool shallow = words > kTileBatchWords && shallowest < kTileBatchDeep;
+    const bool shallow = bands_take(words, shallowest);
     if (e->tiles && shallow && b->shallow) e->tiles = false;
     b->shallow = shallow;
     // the tables hold while nobody else steps the members and their step

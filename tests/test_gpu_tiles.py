@@ -135,7 +135,7 @@ def test_batch_tiles_match_single_steps(rules, solid):
 
 def test_large_batch_between_tiles_and_bands():
     """More words than tiles take for shallow calls: deep, shallow, shallow, deep."""
-    ms = [dict(width=8192, height=8192, seed=k, fill=0.3) for k in range(3)]
+    ms = [dict(width=8192, height=8192, seed=k, fill=0.3) for k in range(5)]
     b = Batch(ms)
     ref = [Sim(**m, depth=1) for m in ms]
     for n in (20, 4, 4, 3, 32, 9):
