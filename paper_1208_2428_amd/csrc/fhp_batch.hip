@@ -543,7 +543,8 @@ struct Engine {
     uint32_t depth_req = kBatchDefaultDepth;  // depth asked for; depth = its effective value
     uint32_t rules = FHP_RULES_FHP2;          // rule set of every member
     int use_graph = 1;
-    // tiled launches instead of sweeping bands (see engine_tiles)
+    // tiled launches instead of sweeping bands (see engine_tiles): set while the
+    // tables' memory holds tiles
     bool tiles = false;
     uint32_t tile_items = 0, tile_n = 0;      // tiles; most steps per launch
     uint32_t tile_done = 0, tile_launches = 0;  // steps and launches since the tables were built
@@ -679,6 +680,7 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
     h.n_done = done;
     // stage into pinned memory (after the previous upload has been consumed)
     FHP_HIP_TRY(hipEventSynchronize(e->staged), "event");
+    e->tiles = false;  // the upload overwrites the tiles' tables
     uint8_t* p = e->stage;
     const size_t bh = sizeof(h), bm = mem.size() * sizeof(MemberDesc),
                  bg = groups.size() * sizeof(GroupDesc), bw = waves.size() * sizeof(WaveDesc);

@@ -54,21 +54,6 @@ struct TileArgs {
     uint32_t chi_and, chi_or;
 };
 
-// One lattice of a tiled launch over many, and one tile of it.
-struct TileMember {
-    uint64_t* buf[2];
-    const uint64_t* S;
-    uint64_t ps, t0, key_chir, key_force;
-    uint32_t thr_force, chi_and, chi_or;
-    uint32_t H, wd, walls, cur;
-    uint32_t steps;  // steps it may still run (kNoStepLimit: no limit)
-    uint32_t T, C, out_words, tiles_x;
-};
-struct TileItem {
-    uint32_t m, tile;
-};
-constexpr uint32_t kNoStepLimit = 0xffffffffu;
-
 namespace {
 
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }

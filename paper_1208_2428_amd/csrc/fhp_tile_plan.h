@@ -1,5 +1,6 @@
-// fhp_tile_plan.h -- host-side choice of the tiled pass's shape (plain C++:
-// also built on the host alone to be checked).
+// fhp_tile_plan.h -- host-side choice of the tiled pass's shape, and the tables
+// of a launch over many lattices (plain C++: also built on the host alone to be
+// checked).
 //
 // A tile holds rows = T + 2 halo rows of C words; one workgroup steps it n
 // times and stores its T x out_words own words.  Deeper launches spread the
@@ -153,5 +154,20 @@ inline TileShape tile_shape(uint32_t H, uint32_t wd, uint32_t n) {
     }
     return best;
 }
+
+// One lattice of a tiled launch over many, and one tile of it.
+struct TileMember {
+    uint64_t* buf[2];
+    const uint64_t* S;
+    uint64_t ps, t0, key_chir, key_force;
+    uint32_t thr_force, chi_and, chi_or;
+    uint32_t H, wd, walls, cur;
+    uint32_t steps;  // steps it may still run (kNoStepLimit: no limit)
+    uint32_t T, C, out_words, tiles_x;
+};
+struct TileItem {
+    uint32_t m, tile;
+};
+constexpr uint32_t kNoStepLimit = 0xffffffffu;
 
 }  // namespace fhp

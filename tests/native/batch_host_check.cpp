@@ -1,0 +1,128 @@
+// The host side of batches and pools (libfhp.so over the stand-in of
+// hip_standin.h): what the tables hold when a kernel that reads them is
+// launched.  The first argument names the check.
+#include <stdio.h>
+
+#include "../../include/fhp.h"
+#include "../../paper_1208_2428_amd/csrc/fhp_groups.h"
+#include "../../paper_1208_2428_amd/csrc/fhp_tile_plan.h"
+#include "hip_standin.h"
+
+#define REQUIRE(c)                                                           \
+    do {                                                                     \
+        if (!(c)) {                                                          \
+            printf("FAILED line %d: %s (%s)\n", __LINE__, #c, fhp_last_error()); \
+            exit(1);                                                         \
+        }                                                                    \
+    } while (0)
+
+namespace {
+
+std::vector<fhp_params> lattices;  // of the batch, or the pool's jobs
+long tile_launches, band_launches;
+
+fhp_params params(uint32_t W, uint32_t H) {
+    fhp_params p;
+    memset(&p, 0, sizeof(p));
+    p.abi_version = FHP_ABI_VERSION;
+    p.width = W;
+    p.height = H;
+    p.seed = 7;
+    p.fill = 0.3;
+    return p;
+}
+
+uint64_t* device(size_t bytes) {
+    void* p = nullptr;
+    if (posix_memalign(&p, 256, bytes)) exit(2);
+    memset(p, 0, bytes);
+    return (uint64_t*)p;
+}
+
+// Every tile of every member once, each member's shape one its lattice can have.
+void check_tiles(const standin::Launch& l) {
+    const auto* M = standin::arg<const fhp::TileMember*>(l, 0);
+    const auto* it = standin::arg<const fhp::TileItem*>(l, 1);
+    const uint32_t n = standin::arg<uint32_t>(l, 4) + standin::arg<uint32_t>(l, 5);
+    std::vector<std::vector<int>> seen;
+    for (uint32_t i = 0; i < l.grid; i++) {
+        const uint32_t m = it[i].m;
+        REQUIRE(m < lattices.size());
+        REQUIRE(M[m].H >= 2 && M[m].wd >= 1 && M[m].T >= 2 && M[m].T % 2 == 0 && M[m].tiles_x >= 1);
+        const uint32_t tiles = (M[m].H + M[m].T - 1) / M[m].T * M[m].tiles_x;
+        if (seen.size() <= m) seen.resize(m + 1);
+        seen[m].resize(tiles);
+        REQUIRE(it[i].tile < tiles && !seen[m][it[i].tile]++);
+        REQUIRE(fhp::tile_threads(2, M[m].T + 2 * fhp::tile_halo(n), M[m].C) <= fhp::kTileBatchThreads);
+        REQUIRE(M[m].out_words == fhp::tile_out_words(M[m].C, M[m].wd));
+    }
+    for (auto& s : seen)
+        for (int k : s) REQUIRE(k == 1);
+}
+
+void check_bands(const standin::Launch& l) {
+    const auto* g = standin::arg<const fhp::GroupDesc*>(l, 2);
+    const auto* w = standin::arg<const fhp::WaveDesc*>(l, 3);
+    bool known = false;
+    for (auto& p : lattices) known |= p.width / 64 == g[0].wd;
+    REQUIRE(known && g[0].nwaves >= 1 && g[0].T >= 2 && w[g[0].first_wave].m < lattices.size());
+}
+
+void launched(const standin::Launch& l) {
+    if (l.name.find("k_tiles") != std::string::npos) {
+        tile_launches++;
+        check_tiles(l);
+    } else if (l.name.find("k_batchILi") != std::string::npos) {
+        band_launches++;
+        check_bands(l);
+    }
+}
+
+struct BatchOf {
+    fhp_batch* b = nullptr;
+    uint64_t* ws;
+    BatchOf() {
+        size_t bytes = 0;
+        REQUIRE(!fhp_batch_workspace_bytes(lattices.data(), (uint32_t)lattices.size(), &bytes));
+        ws = device(bytes);
+        REQUIRE(!fhp_batch_create(lattices.data(), (uint32_t)lattices.size(), ws, bytes, nullptr, &b));
+    }
+    ~BatchOf() {
+        fhp_batch_destroy(b);
+        free(ws);
+    }
+    void step(uint64_t n) { REQUIRE(!fhp_batch_step(b, n)); }
+    void tiling(uint32_t depth) { REQUIRE(!fhp_batch_set_tiling(b, depth, 0, 0, 1)); }
+};
+
+// Tiles are launched over tiles' tables whatever was set or asked in between.
+void retile() {
+    for (int i = 0; i < 3; i++) lattices.push_back(params(320, 96 + 32 * i));
+    for (uint32_t depth : {0u, 3u}) {
+        BatchOf a;
+        a.step(16);
+        a.tiling(depth);
+        if (depth) a.step(7);
+        a.tiling(0);
+        a.step(16);
+        a.step(5);
+        a.tiling(0);
+        a.step(3);
+    }
+    BatchOf z;
+    z.step(16);
+    z.step(0);
+    z.step(16);
+    REQUIRE(tile_launches == 4 + 4 + 2);
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    standin::on_launch = launched;
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "retile") retile();
+    else return 2;
+    printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
+    return 0;
+}

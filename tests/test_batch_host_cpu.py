@@ -1,0 +1,39 @@
+"""Host side of batches and pools, without a GPU: libfhp.so runs over a stand-in
+for the HIP runtime (native/hip_standin.h), which shows every launch and what
+its tables hold."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1208_2428_amd import _binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = "/opt/rocm"
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    if not shutil.which("g++") or not os.path.isdir(os.path.join(ROCM, "include", "hip")):
+        pytest.skip("g++ or the HIP headers are not available")
+    if not os.path.exists(B.lib_path()):
+        from paper_1208_2428_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("host") / "batch_host_check")
+    lib = os.path.abspath(B.lib_path())
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-rdynamic", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(ROCM, "include"), os.path.join(HERE, "native", "batch_host_check.cpp"),
+                    lib, "-Wl,-rpath," + os.path.dirname(lib), "-Wl,-rpath," + os.path.join(ROCM, "lib"),
+                    "-Wl,--allow-shlib-undefined", "-o", exe], check=True)
+
+    def run(name):
+        r = subprocess.run([exe, name], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.startswith("OK"), (r.returncode, r.stdout, r.stderr)
+    return run
+
+
+def test_tiles_are_launched_over_tile_tables(check):
+    """A tiling set between tiled steps, or a call of no steps, leaves bands in
+    the tables' memory: the next tiled step has to build its own again."""
+    check("retile")
