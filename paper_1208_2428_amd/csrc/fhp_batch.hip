@@ -26,7 +26,7 @@
 //
 // With the default tiling, batches and pools step as tiles of all members
 // instead (k_tiles, fhp_tile.h), one ordinary launch per up to 16 steps or per
-// tick; engine_tiles says where.
+// tick; bands_take says where.
 #include <stdlib.h>
 #include <string.h>
 
@@ -530,6 +530,10 @@ uint32_t batch_default_band(const fhp_sim* sims, uint32_t n, uint32_t K) {
 namespace fhp {
 namespace {
 
+// What the tables' memory holds: tables in place for launches of bands or of
+// tiles, or neither (nothing written yet, or a write that failed).
+enum class Tables { kNone, kBands, kTiles };
+
 struct Engine {
     hipStream_t st = nullptr;
     BatchHeader* hdr = nullptr;
@@ -543,9 +547,8 @@ struct Engine {
     uint32_t depth_req = kBatchDefaultDepth;  // depth asked for; depth = its effective value
     uint32_t rules = FHP_RULES_FHP2;          // rule set of every member
     int use_graph = 1;
-    // tiled launches instead of sweeping bands (see engine_tiles): set while the
-    // tables' memory holds tiles
-    bool tiles = false;
+    Tables held = Tables::kNone;
+    // tiled launches instead of sweeping bands (see engine_tiles)
     uint32_t tile_items = 0, tile_n = 0;      // tiles; most steps per launch
     uint32_t tile_done = 0, tile_launches = 0;  // steps and launches since the tables were built
     // current tables
@@ -680,7 +683,7 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
     h.n_done = done;
     // stage into pinned memory (after the previous upload has been consumed)
     FHP_HIP_TRY(hipEventSynchronize(e->staged), "event");
-    e->tiles = false;  // the upload overwrites the tiles' tables
+    e->held = Tables::kNone;
     uint8_t* p = e->stage;
     const size_t bh = sizeof(h), bm = mem.size() * sizeof(MemberDesc),
                  bg = groups.size() * sizeof(GroupDesc), bw = waves.size() * sizeof(WaveDesc);
@@ -695,6 +698,7 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
     FHP_HIP_TRY(hipEventRecord(e->staged, e->st), "event");
     if (done > e->n_done)  // counters beyond the previous tables may be stale
         FHP_HIP_TRY(launch_fill_u64((uint64_t*)e->done, (done + 1) / 2, 0, e->st), "clear");
+    e->held = Tables::kBands;
     e->nt = nt;
     e->n_groups = h.n_groups;
     e->n_done = done;
@@ -728,19 +732,21 @@ bool bands_take(uint64_t words, uint32_t n_min) {
     return n_min < kTileBatchDeep && ((x > 0.73 && x <= 0.9) || x > 1.19);
 }
 
-// Decides between tiles and bands for sims[0..n) and launches of `n_min` to
-// `n_max` steps and, for tiles, builds and uploads the tables.  limit: steps
-// each may still run, or nullptr.  Leaves e->tiles.
-int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_t n, uint32_t n_min,
-                 uint32_t n_max) {
-    e->tiles = false;
-    if (n == 0 || n > e->max_members) return FHP_OK;
+uint64_t words_of(fhp_sim* const* sims, uint32_t n) {
     uint64_t words = 0;
-    for (uint32_t i = 0; i < n; i++) {
-        words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
+    for (uint32_t i = 0; i < n; i++) words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
+    return words;
+}
+
+// Builds and uploads the tables of tiled launches of up to `n_max` steps over
+// sims[0..n), where they fit (*fit; otherwise the tables stay as they are).
+// limit: steps each may still run, or nullptr.
+int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_t n, uint32_t n_max,
+                 bool* fit) {
+    *fit = false;
+    if (n == 0 || n > e->max_members) return FHP_OK;
+    for (uint32_t i = 0; i < n; i++)
         if ((uint64_t)sims[i]->L.W * sims[i]->L.H > kTileNodes) return FHP_OK;
-    }
-    if (bands_take(words, n_min)) return FHP_OK;
     std::vector<TileShape> shapes(n);
     uint64_t items = 0;
     for (uint32_t i = 0; i < n; i++) {
@@ -784,10 +790,12 @@ int engine_tiles(Engine* e, fhp_sim* const* sims, const uint64_t* limit, uint32_
         force |= s->D.thr_force != 0;
         solid |= s->has_mask || s->L.walls;
     }
+    e->held = Tables::kNone;
     FHP_HIP_TRY(hipMemcpyAsync(e->members, M, bm, hipMemcpyHostToDevice, e->st), "upload");
     FHP_HIP_TRY(hipMemcpyAsync(e->groups, e->stage + bm, bi, hipMemcpyHostToDevice, e->st), "upload");
     FHP_HIP_TRY(hipEventRecord(e->staged, e->st), "event");
-    e->tiles = true;
+    e->held = Tables::kTiles;
+    *fit = true;
     e->tile_items = (uint32_t)items;
     e->tile_n = n_max;
     e->tile_done = e->tile_launches = 0;
@@ -960,9 +968,10 @@ struct fhp_batch {
     std::vector<fhp_sim*> ptrs;
     uint64_t* aux;
     Engine eng;
-    bool tables_dirty;  // tiling changed: rebuild before the next step
+    uint64_t words;     // of all members
     bool own_tiling;    // the caller chose the tiling: sweeping bands
     bool shallow;       // the last call's launches were too shallow for its words as tiles
+    uint32_t unfit;     // bit k: tiles of launches of k steps do not fit the tables
     int changed;        // set by member handles when a member is changed alone
 };
 
@@ -1031,34 +1040,40 @@ int batch_layout(const fhp_params* ps, uint32_t n, BatchLayout* bl) {
 int batch_rebuild(fhp_batch* b) {
     int rc = engine_build(&b->eng, b->ptrs.data(), nullptr, b->n);
     if (rc) return rc;
-    b->tables_dirty = false;
     b->changed = 0;
     return FHP_OK;
 }
 
-// n steps of every member in tiled launches, where the batch takes them
-// (eng.tiles).  The launches are evenly deep, at most kBatchTileSteps steps.
+// n steps of every member in tiled launches, where tiles are faster than bands
+// (*took).  The launches are evenly deep, at most kBatchTileSteps steps.
 constexpr uint32_t kBatchTileSteps = 16;
-int batch_step_tiles(fhp_batch* b, uint64_t n) {
+static_assert(kBatchTileSteps < 32, "fhp_batch.unfit has a bit per depth");
+int batch_step_tiles(fhp_batch* b, uint64_t n, bool* took) {
+    *took = false;
     Engine* e = &b->eng;
     const uint64_t launches = (n + kBatchTileSteps - 1) / kBatchTileSteps;
     const uint32_t shallowest = (uint32_t)(n / launches), deepest = (uint32_t)((n + launches - 1) / launches);
-    // A second call in a row that bands step faster goes back to them; a
-    // single one does not change tables.
-    uint64_t words = 0;
-    for (uint32_t i = 0; i < b->n; i++) words += (uint64_t)b->sims[i].L.H * b->sims[i].L.wd;
-    const bool shallow = bands_take(words, shallowest);
-    if (e->tiles && shallow && b->shallow) e->tiles = false;
-    b->shallow = shallow;
     // the tables hold while nobody else steps the members and their step
     // counter has room
-    if (!e->tiles || b->changed || e->tile_n < deepest || e->tile_done + n >= kTimeLimit) {
-        int rc = engine_tiles(e, b->ptrs.data(), nullptr, b->n, shallowest, deepest);
+    const bool held = e->held == Tables::kTiles && !b->changed && e->tile_n >= deepest &&
+                      e->tile_done + n < kTimeLimit;
+    // A second call in a row that bands step faster goes back to them; a
+    // single one does not change tables.
+    const bool shallow = bands_take(b->words, shallowest), again = shallow && b->shallow;
+    b->shallow = shallow;
+    if (shallow && (again || !held)) return FHP_OK;
+    if (!held) {
+        if (b->unfit >> deepest & 1) return FHP_OK;
+        bool fit;
+        int rc = engine_tiles(e, b->ptrs.data(), nullptr, b->n, deepest, &fit);
         if (rc) return rc;
-        b->tables_dirty = true;  // the band tables are gone
+        if (!fit) {
+            b->unfit |= 1u << deepest;
+            return FHP_OK;
+        }
         b->changed = 0;
-        if (!e->tiles) return FHP_OK;
     }
+    *took = true;
     uint64_t rest = n;
     for (uint64_t left = launches; left > 0; left--) {
         const uint32_t k = (uint32_t)((rest + left - 1) / left);
@@ -1134,6 +1149,7 @@ int fhp_batch_create(const fhp_params* ps, uint32_t n, void* dev_ws, size_t ws_b
         b->ptrs.push_back(&b->sims[i]);
     }
     if (!rc) {
+        b->words = words_of(b->ptrs.data(), n);
         b->eng.band = batch_default_band(b->sims, n, b->eng.depth);
         rc = batch_rebuild(b);
     }
@@ -1173,12 +1189,13 @@ int fhp_batch_step(fhp_batch* b, uint64_t n) {
     for (uint32_t i = 0; i < b->n; i++)
         if (b->sims[i].t + n >= kTimeLimit)
             return fail(FHP_E_STATE, "member %u: time would reach 2^24", i);
-    if (!b->own_tiling && n) {
-        int rc = batch_step_tiles(b, n);
-        if (rc) return rc;
-        if (b->eng.tiles) return FHP_OK;
+    if (n == 0) return FHP_OK;
+    if (!b->own_tiling) {
+        bool took;
+        int rc = batch_step_tiles(b, n, &took);
+        if (rc || took) return rc;
     }
-    if (b->tables_dirty || b->changed) {
+    if (b->eng.held != Tables::kBands || b->changed) {
         int rc = batch_rebuild(b);
         if (rc) return rc;
     }
@@ -1324,14 +1341,15 @@ int fhp_pool_admit(fhp_pool* pl, const fhp_params* p, uint64_t steps, uint32_t* 
 
 namespace {
 
-// A tick of `passes` passes as one tiled launch, where the pool takes tiles
-// (eng.tiles): passes * K steps of every job, and the rest of those left with
+// A tick of `passes` passes as one tiled launch, where tiles are faster than
+// bands (*took): passes * K steps of every job, and the rest of those left with
 // fewer than K.
-int pool_tick_tiles(fhp_pool* pl, uint32_t passes) {
+int pool_tick_tiles(fhp_pool* pl, uint32_t passes, bool* took) {
+    *took = false;
     Engine* e = &pl->eng;
     const uint32_t K = e->depth, n = passes * K, tail = K - 1;
-    if (!pl->changed && !e->tiles) return FHP_OK;  // bands, chosen with these jobs
-    if (pl->changed || !e->tiles || e->tile_n < n + tail) {
+    if (!pl->changed && e->held != Tables::kTiles) return FHP_OK;  // bands, chosen with these jobs
+    if (pl->changed || e->tile_n < n + tail) {
         std::vector<fhp_sim*> act;
         std::vector<uint64_t> lim;
         pl->table_slots.clear();
@@ -1342,14 +1360,18 @@ int pool_tick_tiles(fhp_pool* pl, uint32_t passes) {
             lim.push_back(s.remaining);
             pl->table_slots.push_back(i);
         }
-        int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n, n + tail);
-        if (rc) return rc;
-        if (!e->tiles) {
+        bool fit = false;
+        if (!bands_take(words_of(act.data(), (uint32_t)act.size()), n)) {
+            int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n + tail, &fit);
+            if (rc) return rc;
+        }
+        if (!fit) {
             pl->changed = 1;  // the band tables are to be built
             return FHP_OK;
         }
         pl->changed = 0;
     }
+    *took = true;
     int rc = engine_tile_launch(e, n, tail);
     if (rc) return rc;
     for (uint32_t i : pl->table_slots) {  // host mirror of what the launch does
@@ -1373,17 +1395,14 @@ int fhp_pool_tick(fhp_pool* pl, uint32_t passes) {
     if (!passes) passes = 1;
     const uint32_t K = pl->eng.depth;
     if (!pl->own_band && passes <= (kTileMaxSteps + 1 - K) / K) {
-        int rc = pool_tick_tiles(pl, passes);
-        if (rc) return rc;
-        if (pl->eng.tiles) return FHP_OK;
-    } else if (pl->eng.tiles) {
-        pl->eng.tiles = false;
-        pl->changed = 1;
+        bool took;
+        int rc = pool_tick_tiles(pl, passes, &took);
+        if (rc || took) return rc;
     }
     // The tables list every job with full passes left and give each its total
     // count of full passes; the device counts them down, so the tables are
     // rebuilt only when jobs arrive or leave.
-    if (pl->changed) {
+    if (pl->changed || pl->eng.held == Tables::kTiles) {
         std::vector<fhp_sim*> act;
         std::vector<uint32_t> lim;
         pl->table_slots.clear();

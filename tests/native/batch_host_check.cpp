@@ -2,6 +2,7 @@
 // hip_standin.h): what the tables hold when a kernel that reads them is
 // launched.  The first argument names the check.
 #include <stdio.h>
+#include <sys/mman.h>
 
 #include "../../include/fhp.h"
 #include "../../paper_1208_2428_amd/csrc/fhp_groups.h"
@@ -32,10 +33,9 @@ fhp_params params(uint32_t W, uint32_t H) {
     return p;
 }
 
-uint64_t* device(size_t bytes) {
-    void* p = nullptr;
-    if (posix_memalign(&p, 256, bytes)) exit(2);
-    memset(p, 0, bytes);
+uint64_t* device(size_t bytes) {  // zeros; pages nobody writes cost nothing
+    void* p = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (p == MAP_FAILED) exit(2);
     return (uint64_t*)p;
 }
 
@@ -81,15 +81,15 @@ void launched(const standin::Launch& l) {
 struct BatchOf {
     fhp_batch* b = nullptr;
     uint64_t* ws;
+    size_t bytes = 0;
     BatchOf() {
-        size_t bytes = 0;
         REQUIRE(!fhp_batch_workspace_bytes(lattices.data(), (uint32_t)lattices.size(), &bytes));
         ws = device(bytes);
         REQUIRE(!fhp_batch_create(lattices.data(), (uint32_t)lattices.size(), ws, bytes, nullptr, &b));
     }
     ~BatchOf() {
         fhp_batch_destroy(b);
-        free(ws);
+        munmap(ws, bytes);
     }
     void step(uint64_t n) { REQUIRE(!fhp_batch_step(b, n)); }
     void tiling(uint32_t depth) { REQUIRE(!fhp_batch_set_tiling(b, depth, 0, 0, 1)); }
@@ -116,12 +116,51 @@ void retile() {
     REQUIRE(tile_launches == 4 + 4 + 2);
 }
 
+// Calls of one kind after another write no tables and wait for nothing, on
+// bands as on tiles.
+void repeat() {
+    auto quiet = [](BatchOf& a, uint64_t n, bool tiles) {
+        a.step(n);
+        a.step(n);
+        const standin::Counts c = standin::counts;
+        const long t = tile_launches;
+        for (int i = 0; i < 4; i++) a.step(n);
+        REQUIRE(standin::counts.copies == c.copies && standin::counts.waits == c.waits);
+        REQUIRE((tile_launches > t) == tiles);
+    };
+    // more words than tiles take in shallow calls
+    for (int i = 0; i < 20; i++) lattices.push_back(params(4096, 4096));
+    {
+        BatchOf a;
+        quiet(a, 5, false);
+        quiet(a, 16, true);
+        quiet(a, 3, false);
+        quiet(a, 40, true);
+        // a single shallow call keeps the tiles
+        const standin::Counts c = standin::counts;
+        a.step(5);
+        a.step(40);
+        REQUIRE(standin::counts.copies == c.copies);
+    }
+    // a member too large for tiles
+    lattices.assign(1, params(16384, 16384));
+    lattices.push_back(params(64, 64));
+    {
+        BatchOf a;
+        for (uint64_t n : {5, 16, 40}) quiet(a, n, false);
+    }
+    lattices.assign(3, params(320, 96));
+    BatchOf a;
+    for (uint64_t n : {5, 16, 3, 40}) quiet(a, n, true);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     standin::on_launch = launched;
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "retile") retile();
+    else if (what == "repeat") repeat();
     else return 2;
     printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
     return 0;

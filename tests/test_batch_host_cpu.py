@@ -37,3 +37,8 @@ def test_tiles_are_launched_over_tile_tables(check):
     """A tiling set between tiled steps, or a call of no steps, leaves bands in
     the tables' memory: the next tiled step has to build its own again."""
     check("retile")
+
+
+def test_repeated_calls_write_no_tables(check):
+    """Steps after steps of one kind leave the tables and the host alone."""
+    check("repeat")
