@@ -364,10 +364,8 @@ __global__ void __launch_bounds__(NT, pair_waves<RULES>()) k_tile2(const uint64_
     tile2<NT, FORCE, SOLID, RULES>(slots, in, out, S, a, tile_of(blockIdx.x, gridDim.x));
 }
 
-// Tiles of many lattices in one launch: workgroup b takes item b.  A lattice
-// takes part with `n` steps, or with the `left` ones it still has where they
-// are at most n + tail.  `done` steps and `launches` launches lie between the
-// tables and this launch.
+// Tiles of many lattices in one launch: workgroup b takes item b.  How many
+// steps its lattice takes part with: tile_item_steps.
 template <bool FORCE, bool SOLID, int RULES>
 __global__ void __launch_bounds__(kTileBatchThreads, pair_waves<RULES>())
     k_tiles(const TileMember* __restrict__ members, const TileItem* __restrict__ items, uint32_t done,
@@ -375,16 +373,15 @@ __global__ void __launch_bounds__(kTileBatchThreads, pair_waves<RULES>())
     __shared__ PairSlot<kTileBatchThreads> slots[2];
     const TileItem it = items[tile_item_of(blockIdx.x, gridDim.x)];
     const TileMember& M = members[it.m];
-    if (M.steps <= done) return;
-    const uint32_t left = M.steps - done;
     TileArgs a;
+    a.steps = tile_item_steps(M.steps, done, launches, n, tail);
+    if (!a.steps) return;
     a.H = M.H;
     a.wd = M.wd;
     a.C = M.C;
     a.out_words = M.out_words;
     a.tiles_x = M.tiles_x;
     a.T = M.T;
-    a.steps = left <= n + tail ? left : n;
     a.halo = (a.steps + 1) & ~1u;  // tile_halo
     a.split = 0;
     a.walls = M.walls;

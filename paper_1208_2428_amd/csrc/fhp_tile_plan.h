@@ -170,4 +170,16 @@ struct TileItem {
 };
 constexpr uint32_t kNoStepLimit = 0xffffffffu;
 
+// Steps that a launch of n steps runs of a lattice whose table entry allows
+// `steps`: n, or all it has left where that is at most n + tail, or none where
+// an earlier launch ran its last ones.  `done` steps and `launches` launches
+// lie between the tables and this launch, all with this tail: a lattice that
+// has at most `tail` left then had at most n + tail before the last one.
+constexpr uint32_t tile_item_steps(uint32_t steps, uint32_t done, uint32_t launches, uint32_t n, uint32_t tail) {
+    if (steps <= done) return 0;
+    const uint32_t left = steps - done;
+    if (launches && left <= tail) return 0;
+    return left <= n + tail ? left : n;
+}
+
 }  // namespace fhp

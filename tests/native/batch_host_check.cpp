@@ -21,6 +21,8 @@ namespace {
 
 std::vector<fhp_params> lattices;  // of the batch, or the pool's jobs
 long tile_launches, band_launches;
+bool all_tiled;  // every step of the check is a tiled one: the kernel's rule keeps tiled_time
+std::map<const uint64_t*, uint64_t> tiled_time;  // by a lattice's first buffer
 
 fhp_params params(uint32_t W, uint32_t H) {
     fhp_params p;
@@ -56,8 +58,15 @@ void check_tiles(const standin::Launch& l) {
         REQUIRE(fhp::tile_threads(2, M[m].T + 2 * fhp::tile_halo(n), M[m].C) <= fhp::kTileBatchThreads);
         REQUIRE(M[m].out_words == fhp::tile_out_words(M[m].C, M[m].wd));
     }
-    for (auto& s : seen)
-        for (int k : s) REQUIRE(k == 1);
+    for (size_t m = 0; m < seen.size(); m++) {
+        for (int k : seen[m]) REQUIRE(k == 1);
+        if (!all_tiled) continue;
+        const uint32_t k = fhp::tile_item_steps(M[m].steps, standin::arg<uint32_t>(l, 2), standin::arg<uint32_t>(l, 3),
+                                                standin::arg<uint32_t>(l, 4), standin::arg<uint32_t>(l, 5));
+        uint64_t& t = tiled_time[M[m].buf[0]];
+        REQUIRE(k == 0 || t == M[m].t0 + standin::arg<uint32_t>(l, 2));
+        t += k;
+    }
 }
 
 void check_bands(const standin::Launch& l) {
@@ -154,6 +163,49 @@ void repeat() {
     for (uint64_t n : {5, 16, 3, 40}) quiet(a, n, true);
 }
 
+// A pool's jobs: what the kernel runs of each in every tick is what the host
+// counts, also while ended jobs stay resident.
+void jobs() {
+    all_tiled = true;
+    for (uint32_t passes = 1; passes <= 5; passes++) {
+        lattices.clear();
+        tiled_time.clear();
+        for (uint32_t i = 0; i < 40; i++) lattices.push_back(params(64 + 64 * (i % 3), 8 + 2 * i));
+        size_t bytes = 0;
+        REQUIRE(!fhp_pool_workspace_bytes(64, 4096, 64 << 20, &bytes));
+        uint64_t* arena = device(bytes);
+        fhp_pool* pl = nullptr;
+        REQUIRE(!fhp_pool_create(arena, bytes, 64, 4096, nullptr, &pl));
+        std::vector<uint32_t> slots;
+        uint64_t longest = 0;
+        for (uint32_t i = 0; i < lattices.size(); i++) {
+            const uint64_t steps = i < 36 ? 1 + i : 20 * i;
+            uint32_t slot;
+            REQUIRE(!fhp_pool_admit(pl, &lattices[i], steps, &slot));
+            slots.push_back(slot);
+            longest = std::max(longest, steps);
+        }
+        uint32_t n_done = 0, done[64];
+        for (uint64_t t = 0; t <= longest + 20; t += 5 * passes) {
+            uint32_t k;
+            REQUIRE(!fhp_pool_tick(pl, passes) && !fhp_pool_done(pl, done, 64, &k));
+            n_done += k;
+            std::map<uint64_t, int> kernel, host;
+            for (auto& q : tiled_time) kernel[q.second]++;
+            for (uint32_t slot : slots) {
+                fhp_sim* s;
+                uint64_t now;
+                REQUIRE(!fhp_pool_member(pl, slot, &s) && !fhp_time(s, &now));
+                host[now]++;
+            }
+            REQUIRE(kernel == host);
+        }
+        REQUIRE(n_done == lattices.size());
+        fhp_pool_destroy(pl);
+        munmap(arena, bytes);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -161,6 +213,7 @@ int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "retile") retile();
     else if (what == "repeat") repeat();
+    else if (what == "jobs") jobs();
     else return 2;
     printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
     return 0;

@@ -42,3 +42,8 @@ def test_tiles_are_launched_over_tile_tables(check):
 def test_repeated_calls_write_no_tables(check):
     """Steps after steps of one kind leave the tables and the host alone."""
     check("repeat")
+
+
+def test_ticks_run_what_the_host_counts(check):
+    """Jobs of every remainder, ended ones kept resident, one to five passes a tick."""
+    check("jobs")

@@ -1,10 +1,11 @@
-"""Batches whose tiling changes between tiled steps: the tables of tiles and of
-bands share their memory, and every member stays on the oracle's path."""
+"""Batches and pools whose tables change, or stay, between tiled steps: tiles and
+bands share the tables' memory, and every lattice stays on the oracle's path."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from paper_1208_2428_amd import Batch, autotune
+from paper_1208_2428_amd import Batch, Pool, autotune
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +56,28 @@ def test_tuned_batch_steps_on(cands, tmp_path, monkeypatch):
     b.step(16)
     check(b)
     b.close()
+
+
+@pytest.mark.parametrize("passes,steps", [(1, 6), (1, 9), (2, 11), (2, 14)])
+def test_ended_job_stays_as_it_ended(passes, steps):
+    """A job that ended with a remainder of a tick is not stepped again while it
+    stays resident beside others: neither buffer changes."""
+    W, H = 320, 130
+    pool = Pool(Pool.arena_bytes_for(4, 256, 4 << 20), max_slots=4, max_bands=256)
+    tables = Pool.arena_bytes_for(4, 256, 0)
+    job = dict(width=W, height=H, seed=5, fill=0.3, force_rate=1e-2)
+    slot = pool.admit(steps, **job)
+    pool.admit(200, **dict(job, seed=6))
+    pool.tick(passes)
+    assert pool.done() == [slot]
+    pool.sync()
+    both = slice(tables, tables + 2 * 7 * ((W // 64 * H + 31) // 32 * 32) * 8)
+    before = pool.arena[both].clone()
+    for _ in range(2):
+        pool.tick(passes)
+    pool.sync()
+    assert torch.equal(pool.arena[both], before)
+    ref = oracle.init(W, H, 5, 0.3)
+    ref, _ = oracle.run(ref, 0, steps, 5, 1e-2, threads=THREADS)
+    np.testing.assert_array_equal(pool.member(slot).get_state(), ref)
+    pool.close()
