@@ -1372,6 +1372,9 @@ int pool_tick_tiles(fhp_pool* pl, uint32_t passes, bool* took) {
         pl->changed = 0;
     }
     *took = true;
+    bool any = false;  // of the tables' jobs with steps left
+    for (uint32_t i : pl->table_slots) any |= pl->slots[i].used && pl->slots[i].remaining;
+    if (!any) return FHP_OK;
     int rc = engine_tile_launch(e, n, tail);
     if (rc) return rc;
     for (uint32_t i : pl->table_slots) {  // host mirror of what the launch does

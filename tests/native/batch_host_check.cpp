@@ -201,6 +201,10 @@ void jobs() {
             REQUIRE(kernel == host);
         }
         REQUIRE(n_done == lattices.size());
+        // nothing is launched once all jobs have ended
+        const standin::Counts c = standin::counts;
+        for (int i = 0; i < 4; i++) REQUIRE(!fhp_pool_tick(pl, passes));
+        REQUIRE(standin::counts.launches == c.launches && standin::counts.copies == c.copies);
         fhp_pool_destroy(pl);
         munmap(arena, bytes);
     }
