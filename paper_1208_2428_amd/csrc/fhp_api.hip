@@ -30,11 +30,12 @@ int upload_bytes(fhp_sim* s, const uint8_t* host, int mask_only) {
     uint8_t* stage = (uint8_t*)s->buf[1 - s->cur];
     uint32_t rows = (uint32_t)(staging_bytes(s) / W);
     if (rows > H) rows = H;
-    FHP_HIP_TRY(launch_fill_u64(s->aux, 1, 0, s->st), "clear aux");
     for (uint32_t r0 = 0; r0 < H; r0 += rows) {
         const uint32_t n = (r0 + rows <= H) ? rows : H - r0;
         FHP_HIP_TRY(hipMemcpyAsync(stage, host + (size_t)r0 * W, (size_t)n * W,
                                    hipMemcpyHostToDevice, s->st), "upload");
+        // after the first copy: in front of it, the copy would wait for it
+        if (r0 == 0) FHP_HIP_TRY(launch_fill_u64(s->aux, 1, 0, s->st), "clear aux");
         FHP_HIP_TRY(launch_pack(stage, r0, n, s->L, s->buf[s->cur], s->S, mask_only, s->aux, s->st),
                     "pack");
         FHP_HIP_TRY(hipStreamSynchronize(s->st), "sync");  // the stage is reused

@@ -1,6 +1,6 @@
-// The host side of batches and pools (libfhp.so over the stand-in of
+// The host side of batches, pools and uploads (libfhp.so over the stand-in of
 // hip_standin.h): what the tables hold when a kernel that reads them is
-// launched.  The first argument names the check.
+// launched, and the order of calls.  The first argument names the check.
 #include <stdio.h>
 #include <sys/mman.h>
 
@@ -210,6 +210,23 @@ void jobs() {
     }
 }
 
+// A state goes up at once, not behind a kernel: every chunk is copied, packed
+// and waited for, the note of obstacles cleared in between and read at the end.
+void upload() {
+    fhp_params p = params(256, 256);
+    size_t bytes = 0;
+    REQUIRE(!fhp_workspace_bytes(&p, &bytes));
+    uint64_t* ws = device(bytes);
+    fhp_sim* s = nullptr;
+    REQUIRE(!fhp_create(&p, ws, bytes, nullptr, &s));
+    const std::vector<uint8_t> state(256 * 256);
+    standin::order.clear();
+    REQUIRE(!fhp_set_state(s, state.data(), state.size(), 0));
+    REQUIRE(standin::order == "cflwclwcw");
+    fhp_destroy(s);
+    munmap(ws, bytes);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -218,6 +235,7 @@ int main(int argc, char** argv) {
     if (what == "retile") retile();
     else if (what == "repeat") repeat();
     else if (what == "jobs") jobs();
+    else if (what == "upload") upload();
     else return 2;
     printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
     return 0;

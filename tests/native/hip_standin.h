@@ -31,6 +31,7 @@ static std::map<const void*, std::string>& kernels() {
     return k;
 }
 static Counts counts;
+static std::string order;  // f fill, l other launch, c copy, w wait, in the order of their calls
 static void (*on_launch)(const Launch&);
 static bool capturing;
 
@@ -75,9 +76,11 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         uint64_t* p = standin::arg<uint64_t*>(l, 0);
         for (size_t i = 0, n = standin::arg<size_t>(l, 1); i < n; i++) p[i] = standin::arg<uint64_t>(l, 2);
         standin::counts.fills++;
+        standin::order += 'f';
         return hipSuccess;
     }
     standin::counts.launches++;
+    standin::order += 'l';
     if (standin::on_launch) standin::on_launch(l);
     return hipSuccess;
 }
@@ -100,11 +103,16 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
 hipError_t hipHostFree(void* p) { return free(p), hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
     standin::counts.copies++;
+    standin::order += 'c';
     return memcpy(d, s, n), hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { return memcpy(d, s, n), hipSuccess; }
 
-hipError_t hipStreamSynchronize(hipStream_t) { return standin::counts.waits++, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+    standin::counts.waits++;
+    standin::order += 'w';
+    return hipSuccess;
+}
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEvent_t)1, hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }

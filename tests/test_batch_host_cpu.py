@@ -47,3 +47,8 @@ def test_repeated_calls_write_no_tables(check):
 def test_ticks_run_what_the_host_counts(check):
     """Jobs of every remainder, ended ones kept resident, one to five passes a tick."""
     check("jobs")
+
+
+def test_an_upload_starts_with_its_copy(check):
+    """No kernel is queued in front of a state's first chunk."""
+    check("upload")
