@@ -177,8 +177,26 @@ uint32_t default_depth(uint32_t H, uint32_t wd, uint32_t simds) {
 // 10.8; 12288^2 13.4, 17.5; 14.6.  Above, a sweep's bands give every SIMD two
 // waves and its bytes per step are fewer: 16384 x 12288 17.6 (tiles 18 by the
 // rate of 12288^2), 16384^2 20.5 (24).
+//
+// Calls of two or three steps are a single pass of either.  A sweep is the
+// faster one where every SIMD gets four rows of close to 64 words (fills_simds),
+// in one band or two.  us, tiles and sweep, two steps and three: 4096^2 7.7,
+// 6.3; 10.1, 8.1; 3968 x 3840 7.9, 7.1; 9.6, 9.0; 3584 x 4032 7.8, 6.9; 9.3,
+// 8.9.  Around that range: 3584^2 6.5, 6.8; 7.7, 8.3; 4096 x 5120 9.5, 9.5;
+// 11.9, 12.4; 2560 x 6144 9.6, 10; 11.6, 13.1.  Rows of 64 words, two rows per
+// SIMD: 2048 rows 5.6, 5.4; 7.1, 6.7; 1984 rows 5.7, 5.7; 6.8, 6.8; and a few
+// more than four: 4608 rows 8.6, 7.9; 11.3, 10.9.  FHP-III, two steps: 4096^2
+// 11.1, 8.4; three steps are as fast as tiles (13.6, 13.2) or faster (4352 rows
+// 14.4, 17.4).
+static bool fills_simds(uint32_t H, uint32_t wd, uint32_t simds) {
+    if (wd > 64 || H > 4 * simds + (wd == 64 ? simds / 2 : 0)) return false;
+    const uint64_t words = (uint64_t)H * wd, full = 4ull * 64 * simds;
+    return words * 100 >= full * 84 || (wd == 64 && words == full / 2);
+}
+
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) {
     if (n < 2 || (uint64_t)L.W * L.H > kTileNodes) return TilePlan{};
+    if (n <= (D.rules == FHP_RULES_FHP3 ? 2 : 3) && fills_simds(L.H, L.wd, simds)) return TilePlan{};
     return tile_plan(L.H, L.wd, simds / 4, D.rules == FHP_RULES_FHP3, D.thr_force != 0, n);
 }
 
@@ -191,6 +209,8 @@ TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) 
 // 27.4 -> 20; 10048 x 16384, 24 -> 32 rows 21.6 -> 18.0.
 void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint32_t* K, uint32_t* T) {
     *K = depth;
+    *T = default_band(L.H, L.wd, simds);
+    if ((uint64_t)L.W * L.H <= kTileNodes) return;  // a short call (plan_tiles)
     if (D.rules == FHP_RULES_FHP3) *K = depth < kMaxDepthFHP3 ? depth : kMaxDepthFHP3;
     else if (depth == FHP_MAX_DEPTH && 7 * L.ps * 8 <= 0xffffffffull) *K = kSweepDepth;
     const uint32_t waves = (L.wd + 63) / 64, cus = simds / 4;

@@ -20,7 +20,7 @@
 namespace {
 
 std::vector<fhp_params> lattices;  // of the batch, or the pool's jobs
-long tile_launches, band_launches;
+long tile_launches, band_launches, sim_tiles, sim_sweeps;  // of batches and pools; of single lattices
 bool all_tiled;  // every step of the check is a tiled one: the kernel's rule keeps tiled_time
 std::map<const uint64_t*, uint64_t> tiled_time;  // by a lattice's first buffer
 
@@ -85,6 +85,8 @@ void launched(const standin::Launch& l) {
         band_launches++;
         check_bands(l);
     }
+    sim_tiles += l.name.find("k_tile1") != std::string::npos || l.name.find("k_tile2") != std::string::npos;
+    sim_sweeps += l.name.find("k_stepk") != std::string::npos;
 }
 
 struct BatchOf {
@@ -210,21 +212,59 @@ void jobs() {
     }
 }
 
+struct SimOf {
+    fhp_sim* s = nullptr;
+    uint64_t* ws;
+    size_t bytes = 0;
+    SimOf(const fhp_params& p) {
+        REQUIRE(!fhp_workspace_bytes(&p, &bytes));
+        ws = device(bytes);
+        REQUIRE(!fhp_create(&p, ws, bytes, nullptr, &s));
+    }
+    ~SimOf() {
+        fhp_destroy(s);
+        munmap(ws, bytes);
+    }
+    // one launch of n steps: whether it was a sweep
+    bool swept(uint64_t n) {
+        const long t = sim_tiles, w = sim_sweeps;
+        REQUIRE(!fhp_step(s, n) && sim_tiles + sim_sweeps == t + w + 1);
+        return sim_sweeps > w;
+    }
+};
+
 // A state goes up at once, not behind a kernel: every chunk is copied, packed
 // and waited for, the note of obstacles cleared in between and read at the end.
 void upload() {
-    fhp_params p = params(256, 256);
-    size_t bytes = 0;
-    REQUIRE(!fhp_workspace_bytes(&p, &bytes));
-    uint64_t* ws = device(bytes);
-    fhp_sim* s = nullptr;
-    REQUIRE(!fhp_create(&p, ws, bytes, nullptr, &s));
+    SimOf a(params(256, 256));
     const std::vector<uint8_t> state(256 * 256);
     standin::order.clear();
-    REQUIRE(!fhp_set_state(s, state.data(), state.size(), 0));
+    REQUIRE(!fhp_set_state(a.s, state.data(), state.size(), 0));
     REQUIRE(standin::order == "cflwclwcw");
-    fhp_destroy(s);
-    munmap(ws, bytes);
+}
+
+// Calls of two and three steps (FHP-III: two): one sweep where its bands fill
+// the device evenly, else tiles, of wide runs of words.
+void shallow() {
+    struct {
+        uint32_t W, H;
+        bool sweep;
+    } const cases[] = {{4096, 4096, true}, {4032, 4090, true},  {3456, 4096, true},  {4096, 3442, true},
+                       {4096, 4608, true}, {4096, 2048, true},  {4096, 4610, false}, {4032, 4098, false},
+                       {4096, 3438, false}, {4096, 2046, false}, {4160, 4032, false}, {2048, 2048, false},
+                       {320, 96, false},   {8192, 2048, false}};
+    for (auto& c : cases)
+        for (uint32_t rules : {FHP_RULES_FHP2, FHP_RULES_FHP1, FHP_RULES_FHP3}) {
+            fhp_params p = params(c.W, c.H);
+            p.rules = rules;
+            SimOf a(p);
+            for (uint64_t n : {2, 3}) REQUIRE(a.swept(n) == (c.sweep && (n == 2 || rules != FHP_RULES_FHP3)));
+            REQUIRE(!a.swept(4));
+            REQUIRE(!fhp_set_depth(a.s, 3) && a.swept(2));
+        }
+    for (uint32_t wd : {16, 24, 28, 31, 32, 40, 48, 64, 110, 128})
+        for (uint32_t H : {1024, 2048, 3072, 4096, 8192})
+            for (uint64_t n : {2, 3}) REQUIRE(fhp::tile_plan(H, wd, 256, false, true, n).C >= 10);
 }
 
 }  // namespace
@@ -236,6 +276,7 @@ int main(int argc, char** argv) {
     else if (what == "repeat") repeat();
     else if (what == "jobs") jobs();
     else if (what == "upload") upload();
+    else if (what == "shallow") shallow();
     else return 2;
     printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
     return 0;

@@ -1,4 +1,4 @@
-"""Host side of batches and pools, without a GPU: libfhp.so runs over a stand-in
+"""Host side of lattices, batches and pools, without a GPU: libfhp.so runs over a stand-in
 for the HIP runtime (native/hip_standin.h), which shows every launch and what
 its tables hold."""
 import os
@@ -52,3 +52,9 @@ def test_ticks_run_what_the_host_counts(check):
 def test_an_upload_starts_with_its_copy(check):
     """No kernel is queued in front of a state's first chunk."""
     check("upload")
+
+
+def test_short_calls(check):
+    """Two and three steps: a sweep at the edges of where it fills the device,
+    tiles beyond them."""
+    check("shallow")
