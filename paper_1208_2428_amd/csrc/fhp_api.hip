@@ -207,12 +207,26 @@ TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) 
 // or the height that gives at least two waves per SIMD (default_band; us per
 // step): 16384 x 12288, 24 rows 18.2 -> 17.8; 15040 x 14002, 26 -> 28 rows
 // 27.4 -> 20; 10048 x 16384, 24 -> 32 rows 21.6 -> 18.0.
-void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint32_t* K, uint32_t* T) {
+//
+// Rows of up to 12 words (tall lattices) leave most lanes idle, and passes of
+// two steps, or of four without forcing or by FHP-I, have registers for three
+// waves per SIMD: rounds say little, and bands of 32 rows (default_band) are
+// faster.  us per call, this rule's bands and 32 rows: 384 x 500000, two steps
+// 307, 274, four without forcing 433, 390, three 334, 348, four with forcing
+// 436, 463; 512 x 524288, two steps 326, 274; 768 x 300000 199, 186, four
+// without forcing 266, 249; 832 x 250000 161, 165; 192, 215.  Rows of four or
+// eight words, one wave per band, sweep four steps faster with this rule's
+// (256 x 1048574 653, 675).
+void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint64_t n, uint32_t* K,
+                uint32_t* T) {
     *K = depth;
     *T = default_band(L.H, L.wd, simds);
     if ((uint64_t)L.W * L.H <= kTileNodes) return;  // a short call (plan_tiles)
     if (D.rules == FHP_RULES_FHP3) *K = depth < kMaxDepthFHP3 ? depth : kMaxDepthFHP3;
     else if (depth == FHP_MAX_DEPTH && 7 * L.ps * 8 <= 0xffffffffull) *K = kSweepDepth;
+    const uint64_t passes = (n + *K - 1) / *K, k = (n + passes - 1) / passes;  // the deepest pass
+    const bool light = D.thr_force == 0 || D.rules == FHP_RULES_FHP1;
+    if (L.wd <= 12 && (k == 2 || (k == 4 && light && 64 % L.wd != 0))) return;
     const uint32_t waves = (L.wd + 63) / 64, cus = simds / 4;
     const uint64_t held = (uint64_t)cus * (waves < 8 ? 8 / waves : 1);  // bands at once
     uint64_t best = ~0ull;
@@ -381,7 +395,7 @@ int fhp_step(fhp_sim* s, uint64_t n) {
     if (s->D.rules == FHP_RULES_FHP3 && depth > kMaxDepthFHP3) depth = kMaxDepthFHP3;
     uint32_t T = s->band ? s->band : default_band(s->L.H, s->L.wd, s->simds);
     const bool own = s->own_depth || s->band || L.wd > kMaxBlockedWords;
-    if (!own) plan_sweep(L, s->D, s->simds, s->depth, &depth, &T);
+    if (!own && n) plan_sweep(L, s->D, s->simds, s->depth, n, &depth, &T);
     while (n > 0) {
         // passes of `depth` steps and a shorter last one, or evenly deep
         const uint64_t left = (n + depth - 1) / depth;

@@ -106,9 +106,10 @@ hipError_t launch_stepk(uint32_t K, const uint64_t* in, uint64_t* out, const Lat
 // `steps` (at most P.n) steps in one tiled pass (fhp_tile1.hip).
 hipError_t launch_tile(const TilePlan& P, uint32_t steps, const uint64_t* in, uint64_t* out,
                        const Lattice& L, const Dyn& D, uint64_t t, hipStream_t st);
-// Depth and band height of the sweeping passes of a lattice of default depth
-// `depth`, where the caller chose neither.
-void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint32_t* K, uint32_t* T);
+// Depth and band height of the sweeping passes for n > 0 steps of a lattice of
+// default depth `depth`, where the caller chose neither.
+void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, uint64_t n, uint32_t* K,
+                uint32_t* T);
 // The tiled passes for n steps of a lattice, or no plan (R = 0) where
 // sweeping bands are faster.
 TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n);

@@ -21,6 +21,7 @@ namespace {
 
 std::vector<fhp_params> lattices;  // of the batch, or the pool's jobs
 long tile_launches, band_launches, sim_tiles, sim_sweeps;  // of batches and pools; of single lattices
+uint32_t sweep_bands;  // of the last single lattice's sweep
 bool all_tiled;  // every step of the check is a tiled one: the kernel's rule keeps tiled_time
 std::map<const uint64_t*, uint64_t> tiled_time;  // by a lattice's first buffer
 
@@ -86,7 +87,7 @@ void launched(const standin::Launch& l) {
         check_bands(l);
     }
     sim_tiles += l.name.find("k_tile1") != std::string::npos || l.name.find("k_tile2") != std::string::npos;
-    sim_sweeps += l.name.find("k_stepk") != std::string::npos;
+    if (l.name.find("k_stepk") != std::string::npos) sim_sweeps++, sweep_bands = l.grid;
 }
 
 struct BatchOf {
@@ -267,6 +268,30 @@ void shallow() {
             for (uint64_t n : {2, 3}) REQUIRE(fhp::tile_plan(H, wd, 256, false, true, n).C >= 10);
 }
 
+// Tall lattices of narrow rows: bands of 32 rows in passes of two steps, and in
+// light ones of four; other passes and wider rows take bands by rounds.
+void tall() {
+    struct {
+        uint32_t W, H, rules;
+        double force;
+        uint64_t n;
+        bool thirty_two;
+    } const cases[] = {
+        {384, 500000, 0, 1e-3, 2, true},  {384, 500000, 0, 1e-3, 3, false},  {384, 500000, 0, 1e-3, 4, false},
+        {384, 500000, 0, 0.0, 4, true},   {384, 500000, 1, 1e-3, 4, true},   {384, 500000, 2, 1e-3, 2, true},
+        {384, 500000, 0, 0.0, 5, false},  {512, 524288, 0, 1e-3, 2, true},   {512, 524288, 0, 0.0, 4, false},
+        {768, 300000, 0, 1e-3, 2, true},  {832, 250000, 0, 1e-3, 2, false},  {832, 250000, 0, 0.0, 4, false},
+    };
+    for (auto& c : cases) {
+        fhp_params p = params(c.W, c.H);
+        p.rules = c.rules;
+        p.force_rate = c.force;
+        SimOf a(p);
+        REQUIRE(a.swept(c.n));
+        REQUIRE((sweep_bands == (c.H + 31) / 32) == c.thirty_two);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -277,6 +302,7 @@ int main(int argc, char** argv) {
     else if (what == "jobs") jobs();
     else if (what == "upload") upload();
     else if (what == "shallow") shallow();
+    else if (what == "tall") tall();
     else return 2;
     printf("OK %ld tiled launches, %ld launches of bands\n", tile_launches, band_launches);
     return 0;

@@ -58,3 +58,8 @@ def test_short_calls(check):
     """Two and three steps: a sweep at the edges of where it fills the device,
     tiles beyond them."""
     check("shallow")
+
+
+def test_bands_of_tall_lattices(check):
+    """Passes of two and four steps over narrow rows."""
+    check("tall")
