@@ -26,7 +26,7 @@
 //
 // With the default tiling, batches and pools step as tiles of all members
 // instead (k_tiles, fhp_tile.h), one ordinary launch per up to 16 steps or per
-// tick; bands_take says where.
+// tick; bands_take_call and bands_take_tick say where.
 #include <stdlib.h>
 #include <string.h>
 
@@ -713,29 +713,53 @@ int engine_build(Engine* e, fhp_sim* const* sims, const uint32_t* limit, uint32_
 static_assert(sizeof(TileMember) <= sizeof(MemberDesc), "tile members use the member table's memory");
 static_assert(sizeof(TileItem) <= sizeof(GroupDesc), "tiles use the group and wave tables' memory");
 
-constexpr uint32_t kTileBatchDeep = 10;
-
-// Tiles against bands, by the shallowest launch (n_min steps) and the members'
-// words.  Launches of 10 steps and more step any batch faster as tiles
-// (random sides up to 2048, us per step at 16 steps, tiles and bands: 60
-// lattices 9.7 and 20.5, 512 61 and 81; with forcing 10.5 and 21.0, 72 and
-// 109).  A launch of 5 to 9 steps recomputes and reloads more halo per step.
-// There a sweep takes what whole rounds of its bands take (two waves per SIMD,
-// 32 rows of 64 words each: kBandRoundWords), however empty they are: tiles
-// are faster unless a round is nearly full, or from 1.2 rounds on (channels,
-// million words: 0.05 1.9 and 19.6, 1.9 16.7 and 25.1, 2.5 22 and 27; 3.2 27.3 and
-// 27.1, 3.5 28.4 and 27.7; 3.9 31 and 36, 4.6 36 and 48, 4.9 39.8 and 39.9; 7.6
-// 60 and 55).
+// Tiles against bands.  A tiled launch recomputes and reloads more halo per step
+// the fewer its steps; a band's pass takes what whole rounds of bands take (two
+// waves per SIMD, 32 rows of 64 words each: kBandRoundWords), however empty
+// they are.  So bands are faster only for one pass of them (n at most the
+// bands' depth K) over rounds that are nearly full or many, and only over even
+// members (band_rows): time of bands over time of tiles, for one pass of K steps of
+//   members          one round, 0.8 full   1.1 rounds   1.3    2      5
+//   2048 x 1024      1.4  (pool 0.86)      1.3 (1.1)    1.2 (0.93)   1.0 (0.8)    0.9 (0.74)
+//   4096^2           1.1  (0.88)           1.2 (1.1)    1.0 (0.93)   0.87 (0.82)  0.8 (0.75)
+//   of random size, sides of whole 32 rows, 128 to 2048
+//                    1.5  (1.4)            1.4 (1.4)    1.4 (1.4)    1.3 (1.4)    1.3 (1.4)
+//   1984 x 1024      pool 1.0, 1.2, 1.1, 1.1, 1.1;  1024^2 1.1, 1.3, 1.2, 1.0, 0.95
+//   2048 x 992 .. 1056, any even height: pool 11, 8.7, 7.8, 5, 2.3
+// (heights without a divisor of at most 32 rows are one band).  A pool's tiles
+// leave room for the last steps of its jobs (n + K - 1), a batch's do not.
+// Batches of rows of 32 words step fewer than K steps faster as tiles (three
+// 1.1 to 1.4, four 1.0 to 1.4), of 64 words from two rounds on as bands (0.8
+// to 0.95); one step, FHP-II's two (1.0 to 1.5) and calls of two passes (1.0 to
+// 2) as tiles.
 constexpr uint64_t kBandRoundWords = 2ull * 1024 * 64 * 32;
-bool bands_take(uint64_t words, uint32_t n_min) {
-    const double x = (double)words / kBandRoundWords;
-    return n_min < kTileBatchDeep && ((x > 0.73 && x <= 0.9) || x > 1.19);
+double band_rounds(uint64_t words) { return (double)words / kBandRoundWords; }
+
+bool bands_take_call(uint64_t words, uint32_t rows, uint32_t n, uint32_t K, uint32_t rules) {
+    const uint32_t least = rules == FHP_RULES_FHP3 ? 2 : 3;
+    return n >= least && n <= K && rows && rows % (n == K ? 32 : 64) == 0 && band_rounds(words) > 1.75;
+}
+
+bool bands_take_tick(uint64_t words, uint32_t rows, uint32_t passes, uint32_t K) {
+    const double x = band_rounds(words);
+    return passes == 1 && K >= 3 && rows && rows % 32 == 0 && ((x > 0.73 && x <= 1.0) || x > 1.19);
 }
 
 uint64_t words_of(fhp_sim* const* sims, uint32_t n) {
     uint64_t words = 0;
     for (uint32_t i = 0; i < n; i++) words += (uint64_t)sims[i]->L.H * sims[i]->L.wd;
     return words;
+}
+
+// The words that all members' rows are multiples of (64, 32 or 0, neither), or 0
+// where a member's bands are higher than 32 rows.
+uint32_t band_rows(const Engine* e, fhp_sim* const* sims, uint32_t n) {
+    uint32_t rows = 64;
+    for (uint32_t i = 0; i < n; i++) {
+        while (rows >= 32 && sims[i]->L.wd % rows) rows /= 2;
+        if (rows < 32 || band_for(sims[i]->L.H, e->band, e->depth) > 32) return 0;
+    }
+    return rows;
 }
 
 // Builds and uploads the tables of tiled launches of up to `n_max` steps over
@@ -969,8 +993,9 @@ struct fhp_batch {
     uint64_t* aux;
     Engine eng;
     uint64_t words;     // of all members
+    uint32_t rows;      // band_rows of the default tiling
     bool own_tiling;    // the caller chose the tiling: sweeping bands
-    bool shallow;       // the last call's launches were too shallow for its words as tiles
+    bool shallow;       // the last call was one that bands step faster
     uint32_t unfit;     // bit k: tiles of launches of k steps do not fit the tables
     int changed;        // set by member handles when a member is changed alone
 };
@@ -1052,14 +1077,15 @@ int batch_step_tiles(fhp_batch* b, uint64_t n, bool* took) {
     *took = false;
     Engine* e = &b->eng;
     const uint64_t launches = (n + kBatchTileSteps - 1) / kBatchTileSteps;
-    const uint32_t shallowest = (uint32_t)(n / launches), deepest = (uint32_t)((n + launches - 1) / launches);
+    const uint32_t deepest = (uint32_t)((n + launches - 1) / launches);
     // the tables hold while nobody else steps the members and their step
     // counter has room
     const bool held = e->held == Tables::kTiles && !b->changed && e->tile_n >= deepest &&
                       e->tile_done + n < kTimeLimit;
     // A second call in a row that bands step faster goes back to them; a
     // single one does not change tables.
-    const bool shallow = bands_take(b->words, shallowest), again = shallow && b->shallow;
+    const bool shallow = launches == 1 && bands_take_call(b->words, b->rows, (uint32_t)n, e->depth, e->rules);
+    const bool again = shallow && b->shallow;
     b->shallow = shallow;
     if (shallow && (again || !held)) return FHP_OK;
     if (!held) {
@@ -1151,6 +1177,7 @@ int fhp_batch_create(const fhp_params* ps, uint32_t n, void* dev_ws, size_t ws_b
     if (!rc) {
         b->words = words_of(b->ptrs.data(), n);
         b->eng.band = batch_default_band(b->sims, n, b->eng.depth);
+        b->rows = band_rows(&b->eng, b->ptrs.data(), n);
         rc = batch_rebuild(b);
     }
     if (rc) {
@@ -1361,8 +1388,9 @@ int pool_tick_tiles(fhp_pool* pl, uint32_t passes, bool* took) {
             pl->table_slots.push_back(i);
         }
         bool fit = false;
-        if (!bands_take(words_of(act.data(), (uint32_t)act.size()), n)) {
-            int rc = engine_tiles(e, act.data(), lim.data(), (uint32_t)act.size(), n + tail, &fit);
+        const uint32_t jobs = (uint32_t)act.size();
+        if (!bands_take_tick(words_of(act.data(), jobs), band_rows(e, act.data(), jobs), passes, K)) {
+            int rc = engine_tiles(e, act.data(), lim.data(), jobs, n + tail, &fit);
             if (rc) return rc;
         }
         if (!fit) {

@@ -140,8 +140,8 @@ void repeat() {
         REQUIRE(standin::counts.copies == c.copies && standin::counts.waits == c.waits);
         REQUIRE((tile_launches > t) == tiles);
     };
-    // more words than tiles take in shallow calls
-    for (int i = 0; i < 20; i++) lattices.push_back(params(4096, 4096));
+    // words that bands take in calls of one pass
+    for (int i = 0; i < 30; i++) lattices.push_back(params(4096, 4096));
     {
         BatchOf a;
         quiet(a, 5, false);
@@ -164,6 +164,46 @@ void repeat() {
     lattices.assign(3, params(320, 96));
     BatchOf a;
     for (uint64_t n : {5, 16, 3, 40}) quiet(a, n, true);
+}
+
+// Bands or tiles, by the members' shapes and the steps of a call or tick.
+void routes() {
+    auto batch = [](uint32_t n, uint32_t W, uint32_t H, uint32_t rules, uint64_t steps) {
+        lattices.assign(n, params(W, H));
+        for (auto& p : lattices) p.rules = rules;
+        BatchOf a;
+        const long t = tile_launches;
+        a.step(steps);
+        return tile_launches > t;
+    };
+    for (uint64_t steps : {3, 4, 5}) REQUIRE(!batch(30, 4096, 4096, FHP_RULES_FHP2, steps));
+    for (uint64_t steps : {1, 2, 6, 9, 10}) REQUIRE(batch(30, 4096, 4096, FHP_RULES_FHP2, steps));
+    for (uint64_t steps : {2, 3}) REQUIRE(!batch(30, 4096, 4096, FHP_RULES_FHP3, steps));
+    for (uint64_t steps : {1, 4}) REQUIRE(batch(30, 4096, 4096, FHP_RULES_FHP3, steps));
+    REQUIRE(batch(28, 4096, 4096, FHP_RULES_FHP2, 5));   // fewer rounds
+    REQUIRE(!batch(60, 2048, 4096, FHP_RULES_FHP2, 5));  // rows of 32 words: a whole pass only
+    REQUIRE(batch(60, 2048, 4096, FHP_RULES_FHP2, 3));
+    REQUIRE(batch(60, 1984, 4096, FHP_RULES_FHP2, 5));   // rows that leave lanes idle
+    REQUIRE(batch(60, 4096, 2018, FHP_RULES_FHP2, 5));   // one band of 2018 rows
+    auto pool = [](uint32_t n, uint32_t W, uint32_t H, uint32_t passes) {
+        lattices.assign(n, params(W, H));
+        size_t bytes = 0;
+        REQUIRE(!fhp_pool_workspace_bytes(n, n * H, (size_t)n * W * H * 2, &bytes));
+        uint64_t* arena = device(bytes);
+        fhp_pool* pl = nullptr;
+        REQUIRE(!fhp_pool_create(arena, bytes, n, n * H, nullptr, &pl));
+        uint32_t slot;
+        for (auto& p : lattices) REQUIRE(!fhp_pool_admit(pl, &p, 100, &slot));
+        const long t = tile_launches;
+        REQUIRE(!fhp_pool_tick(pl, passes));
+        fhp_pool_destroy(pl);
+        munmap(arena, bytes);
+        return tile_launches > t;
+    };
+    for (uint32_t n : {94, 128, 153, 300}) REQUIRE(!pool(n, 2048, 1024, 1));
+    for (uint32_t n : {1, 93, 129, 152}) REQUIRE(pool(n, 2048, 1024, 1));
+    REQUIRE(pool(300, 2048, 1024, 2) && pool(300, 1984, 1024, 1) && pool(300, 1024, 2048, 1));
+    REQUIRE(pool(300, 2048, 1018, 1));
 }
 
 // A pool's jobs: what the kernel runs of each in every tick is what the host
@@ -299,6 +339,7 @@ int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "retile") retile();
     else if (what == "repeat") repeat();
+    else if (what == "routes") routes();
     else if (what == "jobs") jobs();
     else if (what == "upload") upload();
     else if (what == "shallow") shallow();

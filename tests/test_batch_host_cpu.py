@@ -44,6 +44,11 @@ def test_repeated_calls_write_no_tables(check):
     check("repeat")
 
 
+def test_routes_by_shape(check):
+    """Bands for one pass over even members and enough rounds, else tiles."""
+    check("routes")
+
+
 def test_ticks_run_what_the_host_counts(check):
     """Jobs of every remainder, ended ones kept resident, one to five passes a tick."""
     check("jobs")
