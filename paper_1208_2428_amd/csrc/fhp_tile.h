@@ -383,6 +383,13 @@ __global__ void __launch_bounds__(kTileBatchThreads, pair_waves<RULES>())
     a.tiles_x = M.tiles_x;
     a.T = M.T;
     a.halo = (a.steps + 1) & ~1u;  // tile_halo
+    // A launch has kTileBatchThreads threads, whatever its tiles take: waves
+    // without a word only keep the barriers, one per step (a 64^2 lattice has
+    // words for one wave of eight).
+    if (!tile_wave_words(uniform(threadIdx.x), a.T + 2 * a.halo, a.C)) {
+        for (uint32_t st = 0; st < a.steps; st++) lds_barrier();
+        return;
+    }
     a.split = 0;
     a.walls = M.walls;
     a.ps = M.ps;

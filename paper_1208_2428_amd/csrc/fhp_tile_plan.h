@@ -36,6 +36,10 @@ inline uint32_t tile_threads(uint32_t R, uint32_t rows, uint32_t C) {
     return R == 1 ? 2 * half : half;
 }
 
+// Whether the wave whose first thread is `thread` has a word of a tile of two rows
+// per thread.
+constexpr bool tile_wave_words(uint32_t thread, uint32_t rows, uint32_t C) { return thread < rows / 2 * C; }
+
 inline uint32_t tile_out_words(uint32_t C, uint32_t wd) { return C == wd ? C : C - 2; }
 inline uint32_t tiles_per_row(uint32_t C, uint32_t wd) {
     const uint32_t o = tile_out_words(C, wd);

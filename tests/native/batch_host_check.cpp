@@ -206,6 +206,21 @@ void routes() {
     REQUIRE(pool(300, 2048, 1018, 1));
 }
 
+// Waves with words of a tile are as many as the shapes' model counts.
+void waves() {
+    for (uint32_t H : {8u, 64u, 96u, 1030u, 4096u})
+        for (uint32_t wd : {1u, 2u, 5u, 16u, 31u, 64u, 128u})
+            for (uint32_t n = 1; n <= 16; n++) {
+                const fhp::TileShape s = fhp::tile_shape(H, wd, n);
+                if (!s.T) continue;
+                const uint32_t rows = s.T + 2 * fhp::tile_halo(n);
+                uint32_t with = 0;
+                for (uint32_t t = 0; t < fhp::kTileBatchThreads; t += 64)
+                    with += fhp::tile_wave_words(t, rows, s.C);
+                REQUIRE(64 * with == fhp::tile_threads(2, rows, s.C));
+            }
+}
+
 // A pool's jobs: what the kernel runs of each in every tick is what the host
 // counts, also while ended jobs stay resident.
 void jobs() {
@@ -339,6 +354,7 @@ int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "retile") retile();
     else if (what == "repeat") repeat();
+    else if (what == "waves") waves();
     else if (what == "routes") routes();
     else if (what == "jobs") jobs();
     else if (what == "upload") upload();

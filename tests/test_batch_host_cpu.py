@@ -49,6 +49,11 @@ def test_routes_by_shape(check):
     check("routes")
 
 
+def test_waves_of_a_tile(check):
+    """Waves with words in a launch over many lattices: those the shapes count."""
+    check("waves")
+
+
 def test_ticks_run_what_the_host_counts(check):
     """Jobs of every remainder, ended ones kept resident, one to five passes a tick."""
     check("jobs")
