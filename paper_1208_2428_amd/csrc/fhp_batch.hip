@@ -1466,8 +1466,9 @@ int fhp_pool_tick(fhp_pool* pl, uint32_t passes) {
             ran[i] = 1;
         }
     }
-    // Jobs left with fewer than K steps finish on the single-lattice kernels;
-    // every job that reached its last step in this tick is reported once.
+    // Jobs left with fewer than K steps finish by fhp_step, in one launch unless
+    // the caller set the member's depth; every job that reached its last step
+    // in this tick is reported once.
     for (uint32_t i = 0; i < pl->slots.size(); i++) {
         PoolSlot& s = pl->slots[i];
         if (!s.used) continue;
@@ -1476,14 +1477,10 @@ int fhp_pool_tick(fhp_pool* pl, uint32_t passes) {
             continue;
         }
         if (s.remaining >= K) continue;
-        const uint32_t r = (uint32_t)s.remaining;
-        const uint32_t depth = s.sim.depth;
-        s.sim.depth = r;
         int* ch = s.sim.changed;
         s.sim.changed = nullptr;
-        int rc = fhp_step(&s.sim, r);
+        int rc = fhp_step(&s.sim, s.remaining);
         s.sim.changed = ch;
-        s.sim.depth = depth;
         if (rc) return rc;
         s.remaining = 0;
         pl->finished.push_back(i);

@@ -204,6 +204,22 @@ void routes() {
     for (uint32_t n : {1, 93, 129, 152}) REQUIRE(pool(n, 2048, 1024, 1));
     REQUIRE(pool(300, 2048, 1024, 2) && pool(300, 1984, 1024, 1) && pool(300, 1024, 2048, 1));
     REQUIRE(pool(300, 2048, 1018, 1));
+    // on bands, jobs left with fewer steps than a pass end in one launch each
+    for (uint64_t rest : {1, 2, 3, 4}) {
+        lattices.assign(130, params(2048, 1024));
+        size_t bytes = 0;
+        REQUIRE(!fhp_pool_workspace_bytes(130, 130 * 32, (size_t)130 * 2048 * 1024 * 2, &bytes));
+        uint64_t* arena = device(bytes);
+        fhp_pool* pl = nullptr;
+        REQUIRE(!fhp_pool_create(arena, bytes, 130, 130 * 32, nullptr, &pl) && !fhp_pool_set_tiling(pl, 0, 32, 0));
+        uint32_t slot, done = 0, list[130];
+        for (auto& p : lattices) REQUIRE(!fhp_pool_admit(pl, &p, 5 + rest, &slot));
+        const standin::Counts c = standin::counts;
+        REQUIRE(!fhp_pool_tick(pl, 1) && !fhp_pool_done(pl, list, 130, &done) && done == 130);
+        REQUIRE(standin::counts.launches == c.launches + 2 + 130);  // header and bands; the rests
+        fhp_pool_destroy(pl);
+        munmap(arena, bytes);
+    }
 }
 
 // Waves with words of a tile are as many as the shapes' model counts.

@@ -24,3 +24,16 @@ def test_short_calls_match_single_steps(W, H, rules):
         assert a.digest() == b.digest(), (n, a.t)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("rules", [0, 1, 2])
+def test_large_lattice_passes_of_every_depth(rules):
+    """Evenly deep passes: single steps, and 4 + 3, 5 + 4 + 4, 6 + 6 + 6 (FHP-III in threes)."""
+    kw = dict(seed=11, fill=0.3, force_rate=5e-3, walls=True, rules=rules)
+    a, b = Sim(16384, 9282, **kw), Sim(16384, 9282, **kw, depth=1)
+    for n in (1, 7, 13, 18):
+        a.step(n)
+        b.step(n)
+        assert a.digest() == b.digest(), (n, a.t)
+    a.close()
+    b.close()
