@@ -60,9 +60,9 @@ inline uint32_t tiles_per_row(uint32_t C, uint32_t wd) {
 //    halves, a workgroup per compute unit.
 // Fitted to launches of 22 lattices from 64^2 to 12288 x 8192 (FHP-II with
 // forcing; FHP-III takes 2.2 or 1.9 times the arithmetic, no forcing 0.87).  Measured
-// us per step of the shape it picks, and of the fastest one found: 256^2 0.52,
-// 0.52; 512^2 0.57, 0.58; 1024^2 0.67, 0.67; 3072^2 1.29, 1.33; 4096^2 1.81,
-// 1.76; 8192 x 8128 6.3, 6.8.
+// us per step of the shape it picks, and of the fastest of all that it
+// considers for 960 steps: 256^2 0.50, 0.50; 512^2 0.55, 0.55; 1024^2 0.67, 0.66;
+// 3072^2 1.31, 1.31; 4096^2 1.81, 1.81; 8192 x 8128 6.25, 6.24.
 inline TilePlan tile_plan(uint32_t H, uint32_t wd, uint32_t cus, bool fhp3, bool force, uint64_t steps) {
     TilePlan best{};
     uint64_t best_lines = 0;
