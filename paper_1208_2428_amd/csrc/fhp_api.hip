@@ -208,6 +208,13 @@ TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) 
 // step): 16384 x 12288, 24 rows 18.2 -> 17.8; 15040 x 14002, 26 -> 28 rows
 // 27.4 -> 20; 10048 x 16384, 24 -> 32 rows 21.6 -> 18.0.
 //
+// Six steps have a kernel with LDS carries only, also for rows of a power of two
+// words up to 64, whose passes of five steps run one wave per band.  us per step
+// there, six and five in bands of the same rule: 4096 x 65536 22.6, 22.7 (without
+// forcing 19.9, 22.3), 4096 x 40000 13.5, 13.6; 2048 x 131072 31.2, 31.2; 1024 x
+// 262144 58.1, 56.9; 512 x 524288 111.0, 108.6; with obstacles 22.5, 23.2; 15.8,
+// 14.2; 33.3, 32.3; 58.4, 57.5; 111.4, 109.5.
+//
 // Rows of up to 12 words (tall lattices) leave most lanes idle, and passes of
 // two steps, or of four without forcing or by FHP-I, have registers for three
 // waves per SIMD: rounds say little, and bands of 32 rows (default_band) are

@@ -26,12 +26,6 @@ hipError_t launch_stepk(uint32_t K, const uint64_t* in, uint64_t* out, const Lat
     // bands of a 4096 x 65536 lattice -25%, 16384^2 at 16 and 32 rows -10% and
     // -8%), and rows of 128 words gain nothing at 4 or 8 rows.
     a.xcd_runs = (L.wd <= 64 && a.T <= 8) ? 1u : 0u;
-    // Six steps have the LDS kernel only, also on rows of a power of two words.
-    // us per step there, six and the one-wave kernel's five in bands of the same
-    // rule: 4096 x 65536 22.6, 22.7 (without forcing 19.9, 22.3), 4096 x 40000
-    // 13.5, 13.6; 2048 x 131072 31.2, 31.2; 1024 x 262144 58.1, 56.9; 512 x
-    // 524288 111.0, 108.6; with obstacles 22.5, 23.2; 15.8, 14.2; 33.3, 32.3;
-    // 58.4, 57.5; 111.4, 109.5.
     if (K == kSweepDepth) return launch_stepk_k6(in, out, L, a, D.rules, st);
     if (planes_wide(L.ps)) return launch_stepk_wide(K, in, out, L, a, D.rules, st);
     // At most one wave per SIMD: nothing hides a wave's load latency, and the
