@@ -247,7 +247,7 @@ def batched_leg(args, plain_at):
     parity = same == len(params) and (vs_oracle is None or vs_oracle == len(params))
     return {"value": res["value"], "unit": "node-updates/s", "lattices": res["lattices"],
             "nodes": res["nodes"], "steps": res["steps"], "tiling": res["tiling"],
-            "timing": "HIP events on the batch stream, graph replay, median of "
+            "timing": "HIP events on the batch stream (graph replay where bands run), median of "
                       f"{len(res['seconds_all'])} runs of {res['steps']} steps",
             "plain_value_same_depth": plain, "ratio_vs_plain": res["value"] / plain,
             "one_by_one_value": one["value"], "ratio_vs_one_by_one": res["value"] / one["value"],

@@ -146,7 +146,8 @@ int fhp_create(const fhp_params *p, void *dev_ws, size_t ws_bytes, void *hip_str
  * HBM (the last pass of a call may be shorter).  0 selects the library's default
  * for this lattice.  While depth and band are both the defaults, fhp_step takes
  * what it finds fastest: tiled launches of up to 32 steps on lattices of up to
- * 12288^2 nodes, on larger ones passes of 6 steps (FHP-III 3) in bands of its
+ * 12288^2 nodes (calls of two or three steps: one sweeping pass where that is
+ * faster), on larger ones passes of 6 steps (FHP-III 3) in bands of its
  * own choice.  fhp_get_depth then returns the nominal depth, which a pass has
  * when a band is set: 3 where the lattice is too small to give every SIMD of the
  * device two waves (as for 4096 x 4096 on 256 compute units), 4 where the
@@ -197,12 +198,13 @@ void fhp_destroy(fhp_sim *s);
 
 /* ---------------------------------------------------------------------------
  * Batches: n independent lattices (any mix of sizes, seeds and parameters)
- * advanced together by one persistent kernel.  Lattices are cut into bands of
- * rows; bands of lattices with the same row width are packed side by side into
- * one workgroup, and a persistent grid takes (pass, band group) work items from
- * a device counter.  With the default tiling throughout, a batch is cut into
- * tiles instead, one launch per up to 16 steps, where that is faster.  With more than one pass per launch, a band waits for its
- * two neighbouring bands' previous pass (per-band counters on the device).
+ * advanced together: with the default tiling as tiles of all members, one launch
+ * per up to 16 steps, unless a call is one that bands step faster; with a tiling
+ * of the caller's by one persistent kernel over bands of rows.  There, bands of
+ * lattices with the same row width are packed side by side into one workgroup,
+ * and the grid takes (pass, band group) work items from a device counter; with
+ * more than one pass per launch, a band waits for its two neighbouring bands'
+ * previous pass (per-band counters on the device).
  * Each member's results are identical to those of a standalone simulation with
  * the same parameters (Sec. 2 model; the same readings as above).
  * Members need width <= 32768, height >= FHP_BATCH_MIN_HEIGHT and seven
@@ -256,10 +258,11 @@ void fhp_batch_destroy(fhp_batch *b);
  * owns a caller-provided device arena (the HBM budget); a job is admitted when
  * a slot, arena memory and band-table room are free, stays resident until it
  * is released, and advances with every tick together with all other resident
- * jobs (one batch-kernel launch per pass over all of them, each job clipped to
- * its remaining steps; the last steps that do not fill a pass run on the
- * single-lattice kernels).  A job's result does not depend on the other jobs
- * or on when it was admitted.  Members need width <= 32768, height >= 8 and
+ * jobs (a tick is one launch of tiles of all of them, their last steps among
+ * them, or where bands are faster one batch-kernel launch per pass, each job
+ * clipped to its remaining steps; the last steps that do not fill a pass then
+ * run on the single-lattice kernels).  A job's result does not depend on the
+ * other jobs or on when it was admitted.  Members need width <= 32768, height >= 8 and
  * seven planes of at most 4 GiB.
  * ------------------------------------------------------------------------- */
 typedef struct fhp_pool fhp_pool;

@@ -1,5 +1,5 @@
-"""Python front end of batches: many lattices advanced by one persistent
-kernel (``fhp_batch_*`` in include/fhp.h)."""
+"""Python front end of batches: many lattices advanced together, as tiles or
+by one persistent kernel over bands (``fhp_batch_*`` in include/fhp.h)."""
 from __future__ import annotations
 
 import ctypes

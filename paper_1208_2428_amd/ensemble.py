@@ -1,7 +1,7 @@
 """The batched ensemble workload: 512 independent periodic lattices with
 sides uniform over the multiples of 64 in [128, 2048], fill uniform in
-[0.1, 0.4], own seeds, 500 steps, advanced by one batch (persistent kernel,
-graph replay, tiling from the autotuner)."""
+[0.1, 0.4], own seeds, 500 steps, advanced by one batch (tiling from the
+autotuner: the library's default, tiles, or bands under graph replay)."""
 from __future__ import annotations
 
 import torch
@@ -23,9 +23,10 @@ def run_batched(params: list[dict], steps: int, tiling: dict | None = None, log=
     state digest after `steps` steps from its initial state.
 
     With no tiling given, tunes on a scratch batch first.  The timed batch
-    first makes one untimed call of `steps` steps, which captures and
-    instantiates its graph; each of the `repeats` timed calls then replays
-    that graph (HIP events on the batch's stream; the median is reported).
+    first makes one untimed call of `steps` steps, which builds its tables or
+    captures its graph; each of the `repeats` timed calls then launches over
+    those tables or replays that graph (HIP events on the batch's stream; the
+    median is reported).
     A second batch, advanced `steps` steps from the initial state with the
     same tiling, gives the digests."""
     if tiling is None:
@@ -37,7 +38,7 @@ def run_batched(params: list[dict], steps: int, tiling: dict | None = None, log=
         if log:
             log(f"ensemble: tuned tiling {tiling}")
     b = Batch(params, **tiling)
-    b.step(steps)  # captures the graph of this launch sequence
+    b.step(steps)  # builds the tables or captures the graph of this launch sequence
     b.sync()
     times = []
     for _ in range(max(1, repeats)):
