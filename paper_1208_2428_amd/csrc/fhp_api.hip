@@ -208,6 +208,11 @@ TilePlan plan_tiles(const Lattice& L, const Dyn& D, uint32_t simds, uint64_t n) 
 // step): 16384 x 12288, 24 rows 18.2 -> 17.8; 15040 x 14002, 26 -> 28 rows
 // 27.4 -> 20; 10048 x 16384, 24 -> 32 rows 21.6 -> 18.0.
 //
+// Passes of two steps over rows of 64 words (one wave per band) have registers
+// for three waves per SIMD, and rounds are counted with those: 4096 x 65536 105
+// -> 95 us per call, 4096 x 40000 61 -> 60, 4096 x 90000 133 -> 129.  (On rows of
+// 16 and 32 words between 11% faster and 3% slower, by the height.)
+//
 // Six steps have a kernel with LDS carries only, also for rows of a power of two
 // words up to 64, whose passes of five steps run one wave per band.  us per step
 // there, six and five in bands of the same rule: 4096 x 65536 22.6, 22.7 (without
@@ -235,12 +240,14 @@ void plan_sweep(const Lattice& L, const Dyn& D, uint32_t simds, uint32_t depth, 
     const bool light = D.thr_force == 0 || D.rules == FHP_RULES_FHP1;
     if (L.wd <= 12 && (k == 2 || (k == 4 && light && 64 % L.wd != 0))) return;
     const uint32_t waves = (L.wd + 63) / 64, cus = simds / 4;
-    const uint64_t held = (uint64_t)cus * (waves < 8 ? 8 / waves : 1);  // bands at once
+    const bool three = k == 2 && L.wd == 64;  // waves per SIMD
+    const uint64_t held = three ? 12ull * cus : (uint64_t)cus * (waves < 8 ? 8 / waves : 1);  // bands at once
+    const uint32_t halo = three ? 4 : 2 * *K;
     uint64_t best = ~0ull;
     *T = 2;
     for (uint32_t t = 8; t <= 128 && t <= L.H; t += 2) {
         const uint64_t bands = (L.H + t - 1) / t;
-        const uint64_t cost = (bands + held - 1) / held * (t + 2 * *K);
+        const uint64_t cost = (bands + held - 1) / held * (t + halo);
         if (cost < best) best = cost, *T = t;
     }
 }

@@ -361,6 +361,11 @@ void tall() {
         REQUIRE(a.swept(c.n));
         REQUIRE((sweep_bands == (c.H + 31) / 32) == c.thirty_two);
     }
+    // rows of 64 words, two steps: whole rounds of three waves per SIMD
+    SimOf a(params(4096, 65536));
+    REQUIRE(a.swept(2));
+    const uint32_t rounds = (sweep_bands + 3071) / 3072;
+    REQUIRE(sweep_bands > rounds * 3072 - 3072 / 20);
 }
 
 }  // namespace

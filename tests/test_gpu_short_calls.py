@@ -8,7 +8,7 @@ from paper_1208_2428_amd import Sim
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(4096, 4096), (4032, 4090), (3456, 4096), (4096, 3442), (4096, 4608), (4096, 2048), (4096, 4610),
-          (3584, 3584), (384, 400000), (512, 300002)]
+          (3584, 3584), (384, 400000), (512, 300002), (4096, 37000)]
 
 
 @pytest.mark.parametrize("rules", [0, 1, 2])
